@@ -1,34 +1,45 @@
-// VALU path, d = 3, T >= 2 explicit steps fused per pass (temporal fusion,
-// paper Sec. "CUDA Core Implementation with Temporal Fusion": the intermediate
+// VALU path, d = 3, T explicit steps fused per pass (temporal fusion, paper
+// Sec. "CUDA Core Implementation with Temporal Fusion": the intermediate
 // fields of the T steps stay on chip, so a pass moves one field in and one out
 // while its arithmetic grows with T, Eq. 8).
 //
-// A workgroup streams down a segment of z planes.  In each plane it computes
-// step 1 on a layout of L1 x M1 points (each thread WY rows x W consecutive
-// columns) and steps 2..T on the same layout; only the layout shrunk by
-// R (T - 1) per side is exact after T steps, and that is the output tile.
+// Work decomposition
+//   A workgroup of NW waves streams a segment of z planes.  Its in-plane
+//   layout is 64 columns x NW*WY rows: a wave owns WY whole rows, a lane one
+//   column of them.  With one column per lane any row length, alignment and
+//   boundary takes the same path (each lane's source column is wrapped or
+//   clamped once per tile), and the x neighbours are the neighbouring lanes.
+//   Columns carry a skirt of R*T per side (BX = 64 - 2RT outputs); rows one of
+//   R*(T-1), because the R input rows above and below the layout are staged.
 //
-// Input staging is cooperative and separate from the compute layout: all
-// threads copy the layout plus its R-point halo, as whole aligned vectors, from
-// HBM into the step-0 LDS plane, a prefetched plane at a time.  The step-1
-// region therefore needs no skirt of its own, and the redundant ring is
-// R (T - 1) wide rather than R T.
+// Step pipeline
+//   Stage 0 takes input plane k (prefetched one plane ahead into registers).
+//   Stage s = 1..T consumes the plane stage s-1 produced one iteration
+//   earlier: the wave's own rows are still in its registers, the R rows above
+//   and below come from the neighbouring waves through LDS, and the column
+//   neighbours by whole-wave DPP rotates or, for the XL farthest columns of a
+//   star, from the wave's own rows in LDS.  It scatters the plane into 2R+1
+//   rotating accumulator planes (input plane z adds w[c][.][.] to output plane
+//   z-c; contributions arrive with z, then rows, then columns ascending) and
+//   emits the completed plane to the next stage or, for stage T, to HBM.  One
+//   barrier per plane, fields double-buffered.
 //
-// The z pipeline is the one of the one-step 3D kernel: step s reads the plane
-// step s-1 wrote one iteration earlier, scatters it into 2R+1 rotating
-// accumulator planes (input plane z adds its in-plane neighbourhood weighted
-// by w[c][.][.] to output plane z-c) and emits the completed plane, either to
-// its own LDS plane (s < T) or to HBM (s = T).  One barrier per plane.
-//
-// Every LDS plane has the same geometry: row 0 is layout row -R, column OX is
-// layout column 0, where OX >= R is chosen so that LDS column 0 sits on a
-// vector boundary of the grid row whenever the output tile does.
+// What bounds it: vector issue.  Keeping a wave's own rows in registers leaves
+// 2R row reads and at most WY row writes of LDS per plane and stage, where
+// reading the whole (WY+2R) x (W+2R) window from LDS had made LDS the limit.
+// 512^3 periodic, GStencil/s, window-from-LDS kernel -> this one:
+//   float32  Star-3D1R T2 833 -> 938     float64  Star-3D2R T2 432 -> 535
+//            Star-3D2R T2 846 -> 866              Star-3D2R T3 461 -> 545
+//            Star-3D2R T3 956 -> 1131             Star-3D3R T2 323 -> 390
+//            Star-3D3R T2 553 -> 761              Box-3D1R  T2 406 -> 516
+//            Box-3D1R  T2 651 -> 828              Box-3D1R  T3 416 -> 568
+//            Box-3D1R  T3 726 -> 848
+// and 97^3 float32 Star-3D1R T2 150 -> 9 us a pass: small grids need narrow
+// tiles and short segments to reach every CU (see rows3d_pick).
 
-#include <hip/hip_bf16.h>
-#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
+#include <algorithm>
 
 #include "internal.h"
 #include "valu_common.h"
@@ -36,457 +47,415 @@
 namespace stl {
 namespace {
 
+constexpr int kRowsMaxWaves = 8;
+constexpr int kRowsMinWaves = 4;
+
+// Geometry of one pass of one grid: output box, tiling and boundary.
 template <typename TC, int K>
-struct Fused3DArgs {
+struct Rows3DArgs {
     const void *src;
     void *dst;
     int n0, n1, n2;
     int oz0, oz1, oy0, oy1, ox0, ox1;
-    int BZ, nty, ntx, nzs, ntiles;
+    int BZ, BY, nty, ntx, nzs, ntiles;
     int periodic;
     TC h;
     TC w[K];
 };
 
-// value of v in lane (lane - 1) (PREV) or (lane + 1) of the same 16-lane
-// row; the row's first (PREV) or last lane receives `edge`
-template <bool PREV>
-__device__ __forceinline__ float lane_row_shift(float v, float edge)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), PREV ? 0x111 : 0x101,
-                                                      0xF, 0xF, false));
-}
-
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-struct Fused3DCfg {
+template <typename TC, int SHAPE, int R, int T, int WY, int XL>
+struct Rows3DCfg {
     static constexpr int K = SHAPE == STENCIL_BOX ? (2 * R + 1) * (2 * R + 1) * (2 * R + 1) : 6 * R + 1;
-    static constexpr int NT = TX * TY;
-    static constexpr int L1 = TY * WY;                      // layout rows
-    static constexpr int M1 = TX * W;                       // layout columns
-    static constexpr int SK = R * (T - 1);                  // exact margin around the output tile
-    static constexpr int SKL = ((SK + W - 1) / W) * W;      // left margin, whole vectors
-    static constexpr int BY = L1 - 2 * SK;                  // output tile rows
-    static constexpr int BX = ((M1 - SKL - SK) / W) * W;    // output tile columns (whole vectors)
-    static constexpr int OX = ((R + W - 1) / W) * W;        // LDS column of layout column 0
-    static constexpr int NV = (OX + M1 + R + W - 1) / W;    // staged vectors per row
-    static constexpr int LDX = NV * W;                      // LDS row pitch
-    static constexpr int LR = L1 + 2 * R;                   // LDS rows
-    static constexpr int PLANE = LR * LDX;
-    static constexpr int NSV = LR * NV;                     // staged vectors per plane
-    static constexpr int NS = (NSV + NT - 1) / NT;          // ... per thread
     static constexpr int Q = 2 * R + 1;
-    // 0: weights in scalar registers; 1: pinned in vector registers (float32
-    // FMAs with a scalar operand issue slower on gfx950)
-    static constexpr int WMODE = (sizeof(TC) * K <= 192 && (sizeof(TC) == 8 || R >= 3)) ? 0 : 1;
-    static_assert(BY > 0 && BX > 0, "layout narrower than the fused margin");
-    static_assert(sizeof(TC) * K <= 256, "large boxes run on the one-step box kernel");
+    static constexpr int SK = R * (T - 1);      // rows of the exact margin, per side
+    static constexpr int BX = 64 - 2 * R * T;   // output columns of a tile
+    static constexpr int NH = (2 * R + kRowsMinWaves - 1) / kRowsMinWaves;  // staged halo rows per wave
+    // rows a wave keeps in LDS: all of them where columns are read back from
+    // there, else the R first and R last ones its neighbours read
+    static constexpr int SR = XL > 0 ? WY : 2 * R;
+    static constexpr int SLOT = SR * 64;
+    static_assert(WY >= R, "a wave's halo rows come from its direct neighbours");
+    static_assert(BX > 0, "tile narrower than its skirt");
+    static_assert(kRowsMinWaves * WY > 2 * SK, "layout lower than its margin");
+    // per field: R halo rows, the waves' rows, R halo rows
+    static constexpr int field(int nw) { return nw * SLOT + 2 * R * 64; }
+    static constexpr int lds_bytes(int nw) { return 2 * T * field(nw) * (int)sizeof(TC); }
+    static_assert(lds_bytes(kRowsMaxWaves) <= 160 * 1024, "fields exceed LDS");
 };
 
-// W consecutive compute-type values to LDS at an address that is a multiple
-// of the vector (LDS rows hold whole vectors).
-template <typename TC, int W>
-__device__ __forceinline__ void store_lds_vec(const RawVec<TC, W> &o, TC *d)
+// Value of the previous / next lane of the wave (whole-wave DPP rotate by one
+// lane; the wrapped value at the wave's ends lies in the column skirt).  The
+// destination's old value is left undefined: every lane is written, and a
+// defined one costs a move per rotate.
+template <bool PREV>
+__device__ __forceinline__ int lane_rot(int v)
 {
-    if constexpr (sizeof(TC) * W == 16 || sizeof(TC) * W == 8)
-        o.store(static_cast<TC *>(__builtin_assume_aligned(d, sizeof(TC) * W)));
-    else
-#pragma unroll
-        for (int j = 0; j < W; ++j) d[j] = o.e[j];
+    return __builtin_amdgcn_mov_dpp(v, PREV ? 0x13C : 0x134, 0xF, 0xF, true);
+}
+template <bool PREV>
+__device__ __forceinline__ float lane_rot(float v)
+{
+    return __int_as_float(lane_rot<PREV>(__float_as_int(v)));
+}
+template <bool PREV>
+__device__ __forceinline__ double lane_rot(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = lane_rot<PREV>((int)(b & 0xffffffffLL)), hi = lane_rot<PREV>((int)(b >> 32));
+    return __longlong_as_double(((long long)(unsigned)lo) | ((long long)hi << 32));
 }
 
 template <int R>
-__device__ __forceinline__ int star3f_index(int axis, int off)
+__device__ __forceinline__ constexpr int star3r_index(int axis, int off)
 {
     return 1 + axis * 2 * R + (off < 0 ? off + R : off + R - 1);
 }
 
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY, bool FAST>
-__device__ __forceinline__ void fused3d_tile(
-    const Fused3DArgs<TC, Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>::K> &a, const int tile,
-    TC (&lds)[T][2][Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>::PLANE])
+// One tile (in-plane tile x plane segment) of one pass, run by the whole
+// workgroup; `lds` holds the double-buffered rows of T fields.
+template <typename TC, int SHAPE, int R, int T, int WY, int XL, int K>
+__device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC (&wk)[K], const int tile, TC *lds)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
-    constexpr int K = Cfg::K, Q = Cfg::Q, NT = Cfg::NT, LDX = Cfg::LDX, PLANE = Cfg::PLANE;
-    constexpr int NS = Cfg::NS, NV = Cfg::NV, SK = Cfg::SK, SKL = Cfg::SKL, OX = Cfg::OX;
-    using Vec = RawVec<TS, W>;
+    using Cfg = Rows3DCfg<TC, SHAPE, R, T, WY, XL>;
+    constexpr int Q = Cfg::Q, SK = Cfg::SK, NH = Cfg::NH, SLOT = Cfg::SLOT;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6;
 
-    const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
     const int tzs = tile / (a.nty * a.ntx);
     const int rem = tile - tzs * (a.nty * a.ntx);
     const int tyi = rem / a.ntx, txi = rem - tyi * a.ntx;
-    const int z0 = a.oz0 + tzs * a.BZ;
-    const int z1 = min(z0 + a.BZ, a.oz1);
-    const int BZe = z1 - z0;
-    const int y0 = a.oy0 + tyi * Cfg::BY;
-    const int ye = min(y0 + Cfg::BY, a.oy1);
-    const int x0 = a.ox0 + txi * Cfg::BX;
-    const int xe = min(x0 + Cfg::BX, a.ox1);
-    const int cy0 = y0 - SK + ty * WY;  // grid row of this thread's first point
-    const int cx0 = x0 - SKL + tx * W;  // grid column of this thread's first point
-    const int sy0 = y0 - SK - R;        // grid row of LDS row 0
-    const int sx0 = x0 - SKL - OX;      // grid column of LDS column 0 (a vector boundary when x0 is)
-
-    const TS *src = static_cast<const TS *>(a.src);
-    TS *dst = static_cast<TS *>(a.dst);
+    const int z0 = a.oz0 + tzs * a.BZ, z1 = min(z0 + a.BZ, a.oz1);
+    const int y0 = a.oy0 + tyi * a.BY, ye = min(y0 + a.BY, a.oy1);
+    const int x0 = a.ox0 + txi * Cfg::BX, xe = min(x0 + Cfg::BX, a.ox1);
     const int n0 = a.n0, n1 = a.n1, n2 = a.n2;
     const bool periodic = a.periodic != 0;
     const TC h = a.h;
+    const int64_t pitch = (int64_t)n1 * n2;
 
-    for (int i = tid; i < T * 2 * PLANE; i += NT) (&lds[0][0][0])[i] = TC(0);
-
-    TC wk[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        wk[k] = a.w[k];
-        if constexpr (Cfg::WMODE == 1) asm volatile("" : "+v"(wk[k]));
-    }
-
-    bool col_in[W], col_store[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const int c = cx0 + j;
-        col_in[j] = c >= 0 && c < n2;
-        col_store[j] = c >= x0 && c < xe;
-    }
-    bool row_in[WY], row_store[WY];
+    // columns: this lane's source (wrapped, or a valid dummy whose value is
+    // replaced by h) and whether it stores
+    const int x = x0 - R * T + lane;
+    const bool col_in = periodic || (x >= 0 && x < n2);
+    const bool col_store = x >= x0 && x < xe;
+    const TC *srcl = static_cast<const TC *>(a.src) + (periodic ? wrap(x, n2) : min(max(x, 0), n2 - 1));
+    TC *dstl = static_cast<TC *>(a.dst) + x;
+    // rows of the wave, the same for all its lanes
+    const int yw = y0 - SK + wv * WY;
+    int64_t roff[WY];
+    unsigned rin = 0;
 #pragma unroll
     for (int i = 0; i < WY; ++i) {
-        const int r = cy0 + i;
-        row_in[i] = r >= 0 && r < n1;
-        row_store[i] = r >= y0 && r < ye;
+        const int y = yw + i;
+        if (periodic || (y >= 0 && y < n1)) rin |= 1u << i;
+        roff[i] = (int64_t)(periodic ? wrap(y, n1) : min(max(y, 0), n1 - 1)) * n2;
     }
-
-    // Fast staging: rows of whole aligned vectors (grid row a multiple of the
-    // vector, tile on a vector boundary).  Every staged vector then lies
-    // wholly inside or wholly outside the grid: periodic ones wrap by whole
-    // vectors, Dirichlet ones outside are h.  Each thread loads its vectors
-    // unconditionally (entries past the plane repeat the last vector; those
-    // outside a Dirichlet grid load a valid dummy) and selects h at the LDS
-    // write, so staging has no per-vector branch and the prefetched loads are
-    // waited for once per 2R+1 planes.  Other tiles (rows not a whole number
-    // of vectors, unaligned sub-regions) stage element by element.
-    constexpr bool fast = FAST;
-    int s_lds[NS], s_row[NS], s_col[NS];
-    bool s_h[NS], s_ok[NS];
+    // input halo rows: row hr = wv + i nw of the 2R rows around the layout
+    // (waves without one load a row of the halo again and do not write it)
+    int64_t hoff[NH];
+    int hlds[NH];
+    bool hin[NH];
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const int e0 = tid + i * NT;
-        s_ok[i] = e0 < Cfg::NSV;
-        const int e = s_ok[i] ? e0 : Cfg::NSV - 1;
-        const int row = e / NV, v = e - (e / NV) * NV;
-        const int gy = sy0 + row, gc = sx0 + v * W;
-        s_lds[i] = row * LDX + v * W;
-        if (periodic) {
-            s_row[i] = wrap(gy, n1);
-            s_col[i] = fast ? wrap(gc, n2) : gc;
-            s_h[i] = false;
-        } else {
-            const bool rin = gy >= 0 && gy < n1;
-            const bool cin = gc >= 0 && gc + W <= n2;
-            s_row[i] = rin ? gy : -1;
-            s_col[i] = gc;
-            s_h[i] = !rin || !cin;  // fast path: the whole vector is h
-            if (fast && s_h[i]) {    // valid dummy source
-                s_row[i] = 0;
-                s_col[i] = 0;
-            }
-        }
+    for (int i = 0; i < NH; ++i) {
+        const int hr = wv + i * nw;
+        const int hc = hr < 2 * R ? hr : 0;
+        const int y = hc < R ? y0 - SK - R + hc : y0 - SK + nw * WY + hc - R;
+        hin[i] = periodic || (y >= 0 && y < n1);
+        hoff[i] = (int64_t)(periodic ? wrap(y, n1) : min(max(y, 0), n1 - 1)) * n2;
+        hlds[i] = hr >= 2 * R ? -1 : (hc < R ? hc * 64 : nw * SLOT + hc * 64) + lane;
     }
-    const int KTOT = BZe + 2 * R * T + T;
+    const int BZe = z1 - z0, KIN = BZe + 2 * R * T, KTOT = KIN + T;
     const int zbase = z0 - R * T;
-    auto plane_ptr = [&](int k) -> const TS * {
-        const int z = zbase + k;
-        return src + (int64_t)(periodic ? wrap(z, n0) : min(max(z, 0), n0 - 1)) * n1 * n2;
-    };
-    auto plane_in = [&](int k) -> bool {
-        const int z = zbase + k;
-        return periodic || (z >= 0 && z < n0);
-    };
+    const int FL = Cfg::field(nw);
+    // the wave's first row in a field; the rows above it and below its last
+    // one are the neighbours' (or the halo)
+    const int own0 = R * 64 + wv * SLOT + lane;
+    const int up0 = own0 - R * 64, dn0 = own0 + SLOT;
 
-    const bool dst_vec = vec_aligned<TS, W>(dst, n2, x0);
-    // LDS offset of this thread's first point inside a plane
-    const int lpos = (R + ty * WY) * LDX + OX + tx * W;
-    // Window edges from the neighbouring lane.  Each lane's single-element
-    // reads of the r columns left and right of its vector all fall in banks
-    // of one residue mod 4 (the row pitch keeps the vectors aligned), a 4-way
-    // conflict.  With rows of 16 threads (one DPP row each) the edges are
-    // the neighbours' own elements: a row shift by one lane, the first and
-    // last lanes of the row taking the LDS value instead; the other lanes
-    // read a dummy element of their own vector, spread over the banks.
-    // Measured on 512^3 float32: Box-3D1R T = 2 / 3 600 -> 651, 642 -> 726,
-    // Star-3D3R T = 2 518 -> 553 GSt/s; Star-3D2R 5-10 % slower (stars need
-    // edges on their middle rows only), Star-3D1R unchanged.
-    constexpr bool XDPP = TX == 16 && R <= W && sizeof(TC) == 4 && (SHAPE == STENCIL_BOX || R >= 3);
-    const int dj = R + ((tx + ty) & (W - 1));
-
-    {
-        auto load_plane = [&](int k, Vec (&v)[NS]) {
-            if constexpr (FAST) {
-                const TS *pl = plane_ptr(k);
+    TC acc[T][Q][WY], own[T][WY], ring[WY], hring[NH];
 #pragma unroll
-                for (int i = 0; i < NS; ++i) v[i].load(pl + (int64_t)s_row[i] * n2 + s_col[i]);
-            }
+    for (int s = 0; s < T; ++s)
+#pragma unroll
+        for (int i = 0; i < WY; ++i) {
+            own[s][i] = TC(0);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) acc[s][q][i] = TC(0);
+        }
+    int zl = periodic ? wrap(zbase, n0) : 0;  // periodic: source plane of the next load
+    auto load_plane = [&](int k) {
+        const int z = periodic ? zl : min(max(zbase + k, 0), n0 - 1);
+        const int64_t zoff = (int64_t)z * pitch;
+        // opaque scalar offsets: the rows' addresses are not worth the vector
+        // registers that hoisting them out of the loop takes (Box-3D1R
+        // float32 T = 2: 117 instead of 80)
+        auto row_at = [&](int64_t off) {
+            off += zoff;
+            asm volatile("" : "+s"(off));
+            return srcl[off];
         };
-        auto stage_plane = [&](int k, const Vec (&v)[NS], TC *w0) {
-            const bool zin = plane_in(k);
-            if constexpr (FAST) {
 #pragma unroll
-                for (int i = 0; i < NS; ++i) {
-                    RawVec<TC, W> o;
+        for (int i = 0; i < WY; ++i) ring[i] = row_at(roff[i]);
 #pragma unroll
-                    for (int j = 0; j < W; ++j) o.e[j] = (s_h[i] || !zin) ? h : to_compute<TC>(v[i].e[j]);
-                    store_lds_vec(o, w0 + s_lds[i]);
-                }
-            } else {
-                const TS *pl = plane_ptr(k);
-#pragma unroll
-                for (int i = 0; i < NS; ++i) {
-                    if (!s_ok[i]) continue;
-                    TC *d = w0 + s_lds[i];
-                    const TS *rowp = pl + (int64_t)(s_row[i] < 0 ? 0 : s_row[i]) * n2;
-#pragma unroll
-                    for (int j = 0; j < W; ++j) {
-                        const int c = s_col[i] + j;
-                        const bool in = zin && s_row[i] >= 0 && c >= 0 && c < n2;
-                        d[j] = periodic ? to_compute<TC>(rowp[wrap(c, n2)]) : (in ? to_compute<TC>(rowp[c]) : h);
-                    }
-                }
-            }
-        };
+        for (int i = 0; i < NH; ++i) hring[i] = row_at(hoff[i]);
+        zl = zl + 1 == n0 ? 0 : zl + 1;
+    };
+    // the wave's rows of a field, to where its neighbours (and itself) read them
+    auto put_row = [&](TC *wr, int i, TC v) {
+        if constexpr (XL > 0) {
+            wr[i * 64] = v;
+        } else {
+            if (i < R) wr[i * 64] = v;
+            if (i >= WY - R) wr[(i - WY + 2 * R) * 64] = v;
+        }
+    };
+    load_plane(0);
 
-        TC acc[T][Q][WY][W];
+    for (int kb = 0; kb < KTOT; kb += Q) {
 #pragma unroll
-        for (int s = 0; s < T; ++s)
+        for (int u = 0; u < Q; ++u) {
+            const int k = kb + u;
+            if (k >= KTOT) break;
+            const int par = k & 1;
+            // stages from T down to 1: each has used its predecessor's rows of
+            // the previous iteration before that one replaces them
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
+            for (int s = T; s >= 1; --s) {
+                const bool active = k >= s + 2 * R * (s - 1) && k < KIN + s;
+                if (!active) continue;
+                const TC *rd = lds + (2 * (s - 1) + (par ^ 1)) * FL;
+                TC up[R], dn[R];
 #pragma unroll
-                for (int i = 0; i < WY; ++i)
-#pragma unroll
-                    for (int j = 0; j < W; ++j) acc[s][q][i][j] = TC(0);
-
-        // prefetch of the next plane (one plane ahead: the plane's compute
-        // covers the load latency, and a deeper ring costs registers)
-        Vec ring[NS];
-        load_plane(0, ring);
-        __syncthreads();
-
-        for (int kb = 0; kb < KTOT; kb += Q) {
-#pragma unroll
-            for (int u = 0; u < Q; ++u) {
-                const int k = kb + u;
-                if (k >= KTOT) break;
-                const int par = k & 1;
-                {
-                    stage_plane(k, ring, &lds[0][par][0]);
-                    // keep the refill of the ring behind the writes that drain it
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (k + 1 < KTOT) load_plane(k + 1, ring);
+                for (int m = 0; m < R; ++m) {
+                    up[m] = rd[up0 + m * 64];
+                    dn[m] = rd[dn0 + m * 64];
                 }
 #pragma unroll
-                for (int s = 1; s <= T; ++s) {
-                    const bool active = k >= s + 2 * R * (s - 1) && k < BZe + 2 * R * T + s;
-                    const int qc = u % Q;
-                    if (active) {
-                        const TC *rb = &lds[s - 1][par ^ 1][lpos - R * LDX - R];
+                for (int wi = 0; wi < WY + 2 * R; ++wi) {
+                    const bool mid = wi >= R && wi < R + WY;  // a row of this wave
+                    TC row[Q];  // columns lane - R .. lane + R
+                    row[R] = wi < R ? up[wi] : (mid ? own[s - 1][wi - R] : dn[wi - R - WY]);
+                    if (SHAPE == STENCIL_BOX || mid) {
 #pragma unroll
-                        for (int wi = 0; wi < WY + 2 * R; ++wi) {
-                            const bool mid = wi >= R && wi < R + WY;
-                            TC row[W + 2 * R];
-                            if constexpr (XDPP) {
-#pragma unroll
-                                for (int j = 0; j < W; ++j) row[R + j] = rb[wi * LDX + R + j];
-#pragma unroll
-                                for (int j = 0; j < R; ++j) {
-                                    row[j] = TC(0);
-                                    row[R + W + j] = TC(0);
-                                }
-                                if (SHAPE == STENCIL_BOX || mid) {
-#pragma unroll
-                                    for (int m = 0; m < R; ++m) {
-                                        const TC lt = rb[wi * LDX + (tx == 0 ? m : dj)];
-                                        const TC rt = rb[wi * LDX + (tx == TX - 1 ? R + W + m : dj)];
-                                        row[m] = lane_row_shift<true>(row[W + m], lt);
-                                        row[R + W + m] = lane_row_shift<false>(row[R + m], rt);
-                                    }
-                                }
+                        for (int m = 1; m <= R; ++m) {
+                            if (m > R - XL) {
+                                row[R - m] = rd[own0 + (wi - R) * 64 - m];
+                                row[R + m] = rd[own0 + (wi - R) * 64 + m];
                             } else {
-#pragma unroll
-                                for (int j = 0; j < W + 2 * R; ++j) {
-                                    const bool need = SHAPE == STENCIL_BOX || mid || (j >= R && j < R + W);
-                                    row[j] = need ? rb[wi * LDX + j] : TC(0);
-                                }
-                            }
-#pragma unroll
-                            for (int c = -R; c <= R; ++c) {
-                                const int q = ((u - c + R) % Q + Q) % Q;
-#pragma unroll
-                                for (int i = 0; i < WY; ++i) {
-                                    const int ao = wi - i - R;
-                                    if (ao < -R || ao > R) continue;
-                                    if constexpr (SHAPE == STENCIL_BOX) {
-#pragma unroll
-                                        for (int bo = -R; bo <= R; ++bo) {
-                                            const TC wv = wk[((c + R) * (2 * R + 1) + (ao + R)) * (2 * R + 1) + (bo + R)];
-#pragma unroll
-                                            for (int j = 0; j < W; ++j)
-                                                acc[s - 1][q][i][j] = fma_c(wv, row[j + bo + R], acc[s - 1][q][i][j]);
-                                        }
-                                    } else {
-                                        if (c != 0) {
-                                            if (ao != 0) continue;  // z arm: own column only
-                                            const TC wv = wk[star3f_index<R>(0, c)];
-#pragma unroll
-                                            for (int j = 0; j < W; ++j)
-                                                acc[s - 1][q][i][j] = fma_c(wv, row[j + R], acc[s - 1][q][i][j]);
-                                        } else if (ao != 0) {  // y arm
-                                            const TC wv = wk[star3f_index<R>(1, ao)];
-#pragma unroll
-                                            for (int j = 0; j < W; ++j)
-                                                acc[s - 1][q][i][j] = fma_c(wv, row[j + R], acc[s - 1][q][i][j]);
-                                        } else {  // x arm with the centre
-#pragma unroll
-                                            for (int bo = -R; bo <= R; ++bo) {
-                                                const TC wv = bo == 0 ? wk[0] : wk[star3f_index<R>(2, bo)];
-#pragma unroll
-                                                for (int j = 0; j < W; ++j)
-                                                    acc[s - 1][q][i][j] = fma_c(wv, row[j + bo + R], acc[s - 1][q][i][j]);
-                                            }
-                                        }
-                                    }
-                                }
-                            }
-                        }
-                        const int zo = zbase + k - s * (1 + R);
-                        if (s < T) {
-                            TC *wr = &lds[s][par][lpos];
-                            const bool zin = zo >= 0 && zo < n0;
-#pragma unroll
-                            for (int i = 0; i < WY; ++i) {
-                                RawVec<TC, W> o;
-#pragma unroll
-                                for (int j = 0; j < W; ++j) {
-                                    TC v = acc[s - 1][qc][i][j];
-                                    if (!periodic && !(zin && row_in[i] && col_in[j])) v = h;
-                                    o.e[j] = v;
-                                }
-                                store_lds_vec(o, wr + i * LDX);
-                            }
-                        } else if (zo >= z0 && zo < z1) {
-                            TS *pl = dst + (int64_t)zo * n1 * n2;
-#pragma unroll
-                            for (int i = 0; i < WY; ++i) {
-                                if (!row_store[i]) continue;
-                                TS *rowp = pl + (int64_t)(cy0 + i) * n2 + cx0;
-                                Vec ov;
-                                bool all = dst_vec;
-#pragma unroll
-                                for (int j = 0; j < W; ++j) {
-                                    ov.e[j] = to_storage<TS>(acc[s - 1][qc][i][j]);
-                                    all = all && col_store[j];
-                                }
-                                if (all) {
-                                    ov.store(rowp);
-                                } else {
-#pragma unroll
-                                    for (int j = 0; j < W; ++j)
-                                        if (col_store[j]) rowp[j] = ov.e[j];
-                                }
+                                row[R - m] = lane_rot<true>(row[R - m + 1]);
+                                row[R + m] = lane_rot<false>(row[R + m - 1]);
                             }
                         }
                     }
 #pragma unroll
-                    for (int i = 0; i < WY; ++i)
+                    for (int c = -R; c <= R; ++c) {
+                        const int q = ((u - c + R) % Q + Q) % Q;
 #pragma unroll
-                        for (int j = 0; j < W; ++j) acc[s - 1][qc][i][j] = TC(0);
+                        for (int i = 0; i < WY; ++i) {
+                            const int ao = wi - i - R;
+                            if (ao < -R || ao > R) continue;
+                            TC &o = acc[s - 1][q][i];
+                            // the first contribution (c = -R, first row and
+                            // column) starts the sum
+                            if constexpr (SHAPE == STENCIL_BOX) {
+#pragma unroll
+                                for (int bo = -R; bo <= R; ++bo) {
+                                    const TC wv_ = wk[((c + R) * Q + (ao + R)) * Q + (bo + R)];
+                                    o = (c == -R && ao == -R && bo == -R) ? wv_ * row[0] : fma_c(wv_, row[bo + R], o);
+                                }
+                            } else if (c != 0) {  // z arm: own column only
+                                if (ao != 0) continue;
+                                const TC wv_ = wk[star3r_index<R>(0, c)];
+                                o = c == -R ? wv_ * row[R] : fma_c(wv_, row[R], o);
+                            } else if (ao != 0) {  // y arm
+                                o = fma_c(wk[star3r_index<R>(1, ao)], row[R], o);
+                            } else {  // x arm with the centre
+#pragma unroll
+                                for (int bo = -R; bo <= R; ++bo)
+                                    o = fma_c(bo == 0 ? wk[0] : wk[star3r_index<R>(2, bo)], row[bo + R], o);
+                            }
+                        }
+                    }
                 }
-                __syncthreads();
+                const int zo = zbase + k - s * (1 + R);
+                const int qc = u % Q;  // accumulator plane completed now
+                if (s < T) {
+                    const bool zin = periodic || (zo >= 0 && zo < n0);
+                    TC *wr = lds + (2 * s + par) * FL + own0;
+#pragma unroll
+                    for (int i = 0; i < WY; ++i) {
+                        const TC v = (zin && ((rin >> i) & 1u) && col_in) ? acc[s - 1][qc][i] : h;
+                        own[s < T ? s : 0][i] = v;
+                        put_row(wr, i, v);
+                    }
+                } else if (zo >= z0 && zo < z1) {
+                    int64_t off = (int64_t)zo * pitch + (int64_t)yw * n2;
+                    asm volatile("" : "+s"(off));
+                    TC *pl = dstl + off;
+#pragma unroll
+                    for (int i = 0; i < WY; ++i) {
+                        const int y = yw + i;
+                        if (y >= y0 && y < ye && col_store) pl[(int64_t)i * n2] = acc[s - 1][qc][i];
+                    }
+                }
             }
+            // stage 0: input plane k and its halo rows become field 0
+            {
+                const bool zin = periodic || (zbase + k >= 0 && zbase + k < n0);
+                TC *wr = lds + par * FL;
+#pragma unroll
+                for (int i = 0; i < WY; ++i) {
+                    const TC v = (zin && ((rin >> i) & 1u) && col_in) ? ring[i] : h;
+                    own[0][i] = v;
+                    put_row(wr + own0, i, v);
+                }
+#pragma unroll
+                for (int i = 0; i < NH; ++i) {
+                    const TC v = (zin && hin[i] && col_in) ? hring[i] : h;
+                    if (hlds[i] >= 0) wr[hlds[i]] = v;
+                }
+                // keep the refill of the ring behind the reads that drain it
+                __builtin_amdgcn_sched_barrier(0);
+                if (k + 1 < KIN) load_plane(k + 1);
+            }
+            __syncthreads();
         }
     }
 }
 
-// Whether a tile takes the fast staging path: rows of whole aligned vectors
-// and a tile starting on a vector boundary.
-template <typename TS, int W, typename A>
-__device__ __forceinline__ bool fused3d_fast(const A &a, int tile, int BX)
+// Float32 weights are pinned in vector registers (float32 FMAs with a scalar
+// operand issue slower on gfx950).
+template <typename TC, int K>
+__device__ __forceinline__ void rows3d_weights(TC (&wk)[K], const TC *w)
 {
-    const int rem = tile % (a.nty * a.ntx);
-    const int x0 = a.ox0 + (rem % a.ntx) * BX;
-    return vec_aligned<TS, W>(a.src, a.n2, 0) && (x0 % W) == 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        wk[k] = w[k];
+        if constexpr (sizeof(TC) == 4) asm volatile("" : "+v"(wk[k]));
+    }
 }
 
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-__global__ __launch_bounds__(TX *TY) void fused3d_kernel(
-    Fused3DArgs<TC, Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>::K> a)
+extern __shared__ __attribute__((aligned(16))) unsigned char rows3d_lds[];
+
+template <typename TC, int SHAPE, int R, int T, int WY, int XL, int MINW>
+__global__ __launch_bounds__(64 * kRowsMaxWaves) __attribute__((amdgpu_waves_per_eu(MINW))) void fused3d_kernel(
+    Rows3DArgs<TC, Rows3DCfg<TC, SHAPE, R, T, WY, XL>::K> a)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
-    __shared__ __attribute__((aligned(16))) TC lds[T][2][Cfg::PLANE];
+    using Cfg = Rows3DCfg<TC, SHAPE, R, T, WY, XL>;
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= a.ntiles) return;
-    if (fused3d_fast<TS, W>(a, tile, Cfg::BX))
-        fused3d_tile<TS, TC, SHAPE, R, T, W, WY, TX, TY, true>(a, tile, lds);
-    else
-        fused3d_tile<TS, TC, SHAPE, R, T, W, WY, TX, TY, false>(a, tile, lds);
+    TC wk[Cfg::K];
+    rows3d_weights<TC, Cfg::K>(wk, a.w);
+    rows3d_tile<TC, SHAPE, R, T, WY, XL, Cfg::K>(a, wk, tile, reinterpret_cast<TC *>(rows3d_lds));
 }
 
-// Persistent batched launch over the tiles of every job of the batch (see the
-// one-step 3D kernel); the tile body ends with a barrier.
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-__global__ __launch_bounds__(TX *TY) void fused3d_batch_kernel(
-    const Fused3DArgs<TC, Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>::K> *__restrict__ jobs,
+// Persistent batched launch: the workgroups walk one list of tiles spanning
+// every job of the batch; workgroup b takes items b + i*gridDim.  tile_start[j]
+// is the first item of job j (tile_start[njobs] = total).  The tile body ends
+// with a barrier, so the LDS rows are free when the next item starts.
+template <typename TC, int SHAPE, int R, int T, int WY, int XL, int MINW>
+__global__ __launch_bounds__(64 * kRowsMaxWaves) __attribute__((amdgpu_waves_per_eu(MINW))) void fused3d_batch_kernel(
+    const Rows3DArgs<TC, Rows3DCfg<TC, SHAPE, R, T, WY, XL>::K> *__restrict__ jobs,
     const int *__restrict__ tile_start, int njobs)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
-    __shared__ __attribute__((aligned(16))) TC lds[T][2][Cfg::PLANE];
+    using Cfg = Rows3DCfg<TC, SHAPE, R, T, WY, XL>;
     const int total = tile_start[njobs];
     int j = 0;
     for (int item = xcd_remap(blockIdx.x, gridDim.x); item < total; item += gridDim.x) {
         while (j + 1 < njobs && tile_start[j + 1] <= item) ++j;
-        const Fused3DArgs<TC, Cfg::K> a = jobs[j];
-        const int tile = item - tile_start[j];
-        if (fused3d_fast<TS, W>(a, tile, Cfg::BX))
-            fused3d_tile<TS, TC, SHAPE, R, T, W, WY, TX, TY, true>(a, tile, lds);
-        else
-            fused3d_tile<TS, TC, SHAPE, R, T, W, WY, TX, TY, false>(a, tile, lds);
+        const Rows3DArgs<TC, Cfg::K> a = jobs[j];
+        TC wk[Cfg::K];
+        rows3d_weights<TC, Cfg::K>(wk, jobs[j].w);
+        rows3d_tile<TC, SHAPE, R, T, WY, XL, Cfg::K>(a, wk, item - tile_start[j], reinterpret_cast<TC *>(rows3d_lds));
     }
 }
 
-// Segment length along z: the number of segments maximises (share of the
-// resident slots the last round keeps busy) x (share of staged planes that
-// are outputs, BZ / (BZ + 2 R T)), with segments of at least max(8 R T, 32)
-// planes (or the whole grid): shorter ones restage and recompute their
-// 2 R T + T lead-in planes too often, which a batched launch of many small
-// grids does not need to fill the GPU.
-inline int fused3d_segments(int D0, int inplane, int slots, int R, int T)
+// Rows per wave, farthest columns read from LDS, and waves per SIMD the
+// registers are held to.  Measured on 512^3 over WY = 4..8, XL = 0..2 and 4 or
+// 8 waves: as many rows as two resident 8-wave workgroups (128 registers;
+// float64 stars with r >= 2: one, 256) have room for, since every row of the
+// margin is recomputed by each tile; XL >= 1 gains 2-11 % where rotates are
+// the larger share (Star-3D2R float32 T = 3 1019 -> 1131) and loses 3 % on
+// Star-3D2R float64 T = 3 and Star-3D1R, whose one rotate per side is cheap.
+template <typename TC, int SHAPE, int R, int T>
+struct Rows3DShape {
+    static constexpr bool F64 = sizeof(TC) == 8, BOX = SHAPE == STENCIL_BOX;
+    static constexpr int WY = F64 ? (BOX || R == 1 ? 4 : (R == 2 && T == 2 ? 6 : 5))
+                                  : (BOX || R == 1 ? (T == 2 ? 4 : 6) : 5);
+    static constexpr int XL = BOX || R == 1 ? 0 : (F64 ? (R == 2 && T == 3 ? 0 : 1) : (R == 2 && T == 3 ? 1 : 2));
+    static constexpr int MINW = F64 && R >= 2 ? 1 : 4;
+};
+
+// One in-plane box of a launch: planes, rows and columns to write.
+struct Box3 {
+    int d0, d1, d2;
+};
+
+struct Rows3DPick {
+    int nw, BZ;
+};
+
+// Waves per workgroup (4 or 8) and planes per segment of a launch over n
+// boxes.  A workgroup takes BZ + 2RT + T plane iterations; one costs the
+// larger of its latency (barrier, LDS, the next plane's loads: about 1000
+// cycles on top of a wave's own arithmetic) and the arithmetic of the waves
+// that share a SIMD.  The estimate is the number of rounds over the resident
+// workgroups times that.  Small grids come out with segments of a few planes
+// that put work on every CU (97^3 float32 Star-3D1R T = 2: 3 planes 8.7 us, 25
+// planes 21.6 us), large ones with segments that amortise the 2RT + T lead-in
+// planes in whole rounds (512^3 Star-3D2R float64 T = 3: 3 segments 545, 4
+// 440, 8 527 GSt/s).
+template <typename Cfg, typename TC, int SHAPE, int R, int T, int WY>
+Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const int (&occ)[2])
 {
-    const int minBZ = 8 * R * T > 32 ? 8 * R * T : 32;
-    int best = 1;
-    double best_score = -1.0;
-    for (int segs = 1; segs <= 256 && segs <= D0; ++segs) {
-        const int BZ = (D0 + segs - 1) / segs;
-        if (segs > 1 && BZ < minBZ) break;
-        const int nzs = (D0 + BZ - 1) / BZ;
-        const int64_t items = (int64_t)nzs * inplane;
-        const int64_t rounds = (items + slots - 1) / slots;
-        const double balance = (double)items / (double)(rounds * slots);
-        const double zeff = (double)BZ / (double)(BZ + 2 * R * T);
-        const double score = balance * zeff;
-        if (score > best_score + 1e-9) {
-            best_score = score;
-            best = segs;
+    const double wave = T * WY * ((sizeof(TC) == 8 ? 5.0 : 4.0) * Cfg::K + 4.0 * (2 * R * (sizeof(TC) / 4) + 4));
+    static const int kSegs[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,  16, 20,
+                                24, 28, 32, 40, 48, 64, 96, 128, 192, 256};
+    int dmax = 1;
+    for (int i = 0; i < n; ++i) dmax = std::max(dmax, boxes[i].d0);
+    Rows3DPick best{kRowsMaxWaves, dmax};
+    double best_cost = -1.0;
+    for (int v = 0; v < 2; ++v) {
+        const int nw = v ? kRowsMaxWaves : kRowsMinWaves, BY = nw * WY - 2 * Cfg::SK;
+        const int slots = cus * occ[v];
+        int last = 0;
+        for (int segs : kSegs) {
+            int BZ = fixed_bz > 0 ? fixed_bz : (dmax + segs - 1) / segs;
+            if (BZ == last) break;
+            last = BZ;
+            double items = 0;
+            for (int i = 0; i < n; ++i)
+                items += (double)((boxes[i].d0 + BZ - 1) / BZ) * ((boxes[i].d1 + BY - 1) / BY) *
+                         ((boxes[i].d2 + Cfg::BX - 1) / Cfg::BX);
+            const double full = (double)(int64_t)(items / slots);
+            const double rest = items - full * slots;
+            auto plane = [&](double resident) {  // cycles of a plane iteration
+                const double perSimd = (double)(int64_t)((resident * nw + 3) / 4);
+                return std::max(1000.0 + wave, wave * perSimd);
+            };
+            double rounds = full * plane(occ[v]);
+            if (rest > 0) rounds += plane((double)(int64_t)((rest + cus - 1) / cus));
+            const double cost = (std::min(BZ, dmax) + 2 * R * T + T) * rounds;
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                best = {nw, BZ};
+            }
         }
     }
     return best;
 }
 
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-bool fused3d_args(const PassArgs &p, int slots,
-                  Fused3DArgs<TC, Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>::K> *out, hipError_t *err)
+inline Box3 box_of(const PassArgs &p)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
+    return {p.region_hi[0] - p.region_lo[0], p.region_hi[1] - p.region_lo[1], p.region_hi[2] - p.region_lo[2]};
+}
+
+// Fill the arguments of one pass; returns false when there is nothing to do
+// (err then says whether the pass is invalid).
+template <typename Cfg, typename TC, int WY>
+bool rows3d_args(const PassArgs &p, Rows3DPick pick, Rows3DArgs<TC, Cfg::K> *out, hipError_t *err)
+{
     *err = hipSuccess;
-    Fused3DArgs<TC, Cfg::K> &a = *out;
+    Rows3DArgs<TC, Cfg::K> &a = *out;
     a.src = p.src;
     a.dst = p.dst;
     a.n0 = (int)p.dims[0];
@@ -501,63 +470,99 @@ bool fused3d_args(const PassArgs &p, int slots,
     a.periodic = p.boundary == STENCIL_PERIODIC;
     a.h = (TC)p.halo;
     for (int k = 0; k < Cfg::K; ++k) a.w[k] = (TC)p.w[k];
-    const int D0 = a.oz1 - a.oz0, D1 = a.oy1 - a.oy0, D2 = a.ox1 - a.ox0;
-    if (D0 <= 0 || D1 <= 0 || D2 <= 0) return false;
-    a.nty = (D1 + Cfg::BY - 1) / Cfg::BY;
-    a.ntx = (D2 + Cfg::BX - 1) / Cfg::BX;
-    int BZ = p.tile_rows;
-    if (BZ <= 0) {
-        const int segs = fused3d_segments(D0, a.nty * a.ntx, slots, R, T);
-        BZ = (D0 + segs - 1) / segs;
-    }
-    a.BZ = BZ;
-    a.nzs = (D0 + BZ - 1) / BZ;
-    const int64_t nt = (int64_t)a.nzs * a.nty * a.ntx;
-    if (nt > (1LL << 30)) {
+    const Box3 b = box_of(p);
+    if (b.d0 <= 0 || b.d1 <= 0 || b.d2 <= 0) return false;
+    a.BY = pick.nw * WY - 2 * Cfg::SK;
+    a.nty = (b.d1 + a.BY - 1) / a.BY;
+    a.ntx = (b.d2 + Cfg::BX - 1) / Cfg::BX;
+    const int64_t inplane = (int64_t)a.nty * a.ntx, most = 1LL << 30;
+    if (inplane > most) {
         *err = hipErrorInvalidValue;
         return false;
     }
-    a.ntiles = (int)nt;
+    // segments of equal length, no more of them than tile ids allow
+    int64_t segs = (b.d0 + pick.BZ - 1) / pick.BZ;
+    if (p.tile_rows > 0) {
+        a.BZ = p.tile_rows;
+        if (segs * inplane > most) {
+            *err = hipErrorInvalidValue;
+            return false;
+        }
+    } else {
+        segs = std::min<int64_t>(segs, most / inplane);
+        a.BZ = (int)((b.d0 + segs - 1) / segs);
+    }
+    a.nzs = (b.d0 + a.BZ - 1) / a.BZ;
+    a.ntiles = (int)(a.nzs * inplane);
     return true;
 }
 
-// resident workgroups per CU x CUs
-template <typename K>
-int fused3d_slots(K kernel, int threads, int num_cu)
+// resident workgroups per CU with 4 and with 8 waves
+template <typename Cfg, typename K>
+struct Rows3DOcc {
+    int occ[2];
+    explicit Rows3DOcc(K kernel)
+    {
+        for (int v = 0; v < 2; ++v) {
+            const int nw = v ? kRowsMaxWaves : kRowsMinWaves;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[v], kernel, 64 * nw, Cfg::lds_bytes(nw)) !=
+                    hipSuccess || occ[v] < 1)
+                occ[v] = 1;
+        }
+    }
+};
+
+template <typename Cfg, typename K>
+hipError_t rows3d_allow_lds(K kernel, int nw)
 {
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1) occ = 1;
-    return occ * (num_cu > 0 ? num_cu : 256);
+    if (Cfg::lds_bytes(nw) <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               Cfg::lds_bytes(nw));
 }
 
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-hipError_t launch_fused3d_cfg(const PassArgs &p, hipStream_t stream)
+template <typename TC, int SHAPE, int R, int T>
+hipError_t launch_fused3d(const PassArgs &p, hipStream_t stream)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
-    static const int slots = fused3d_slots(fused3d_kernel<TS, TC, SHAPE, R, T, W, WY, TX, TY>, TX * TY,
-                                           p.num_cu);
-    Fused3DArgs<TC, Cfg::K> a;
+    using S = Rows3DShape<TC, SHAPE, R, T>;
+    using Cfg = Rows3DCfg<TC, SHAPE, R, T, S::WY, S::XL>;
+    const auto kernel = fused3d_kernel<TC, SHAPE, R, T, S::WY, S::XL, S::MINW>;
+    static const Rows3DOcc<Cfg, decltype(kernel)> occ(kernel);
+    const Box3 b = box_of(p);
+    const Rows3DPick pick = rows3d_pick<Cfg, TC, SHAPE, R, T, S::WY>(&b, 1, p.tile_rows, p.num_cu > 0 ? p.num_cu : 256,
+                                                                     occ.occ);
+    Rows3DArgs<TC, Cfg::K> a;
     hipError_t err;
-    if (!fused3d_args<TS, TC, SHAPE, R, T, W, WY, TX, TY>(p, slots, &a, &err)) return err;
-    hipLaunchKernelGGL((fused3d_kernel<TS, TC, SHAPE, R, T, W, WY, TX, TY>), dim3(a.ntiles), dim3(TX * TY), 0,
-                       stream, a);
+    if (!rows3d_args<Cfg, TC, S::WY>(p, pick, &a, &err)) return err;
+    err = rows3d_allow_lds<Cfg>(kernel, pick.nw);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3(a.ntiles), dim3(64 * pick.nw), Cfg::lds_bytes(pick.nw), stream, a);
     return hipGetLastError();
 }
 
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, int WY, int TX, int TY>
-hipError_t launch_fused3d_batch_cfg(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+template <typename TC, int SHAPE, int R, int T>
+hipError_t launch_fused3d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    using Cfg = Fused3DCfg<TS, TC, SHAPE, R, T, W, WY, TX, TY>;
-    using Args = Fused3DArgs<TC, Cfg::K>;
-    static const int slots = fused3d_slots(fused3d_batch_kernel<TS, TC, SHAPE, R, T, W, WY, TX, TY>,
-                                           TX * TY, ps[0].num_cu);
+    using S = Rows3DShape<TC, SHAPE, R, T>;
+    using Cfg = Rows3DCfg<TC, SHAPE, R, T, S::WY, S::XL>;
+    using Args = Rows3DArgs<TC, Cfg::K>;
+    const auto kernel = fused3d_batch_kernel<TC, SHAPE, R, T, S::WY, S::XL, S::MINW>;
+    static const Rows3DOcc<Cfg, decltype(kernel)> occ(kernel);
+    const int cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
+    std::vector<Box3> boxes;
+    for (int i = 0; i < n; ++i) {
+        const Box3 b = box_of(ps[i]);
+        if (b.d0 > 0 && b.d1 > 0 && b.d2 > 0) boxes.push_back(b);
+    }
+    if (boxes.empty()) return hipSuccess;
+    const Rows3DPick pick =
+        rows3d_pick<Cfg, TC, SHAPE, R, T, S::WY>(boxes.data(), (int)boxes.size(), 0, cus, occ.occ);
     std::vector<Args> jobs;
     std::vector<int> start(1, 0);
     jobs.reserve(n);
     for (int i = 0; i < n; ++i) {
         Args a;
         hipError_t err;
-        if (!fused3d_args<TS, TC, SHAPE, R, T, W, WY, TX, TY>(ps[i], slots, &a, &err)) {
+        if (!rows3d_args<Cfg, TC, S::WY>(ps[i], {pick.nw, ps[i].tile_rows > 0 ? ps[i].tile_rows : pick.BZ}, &a, &err)) {
             if (err != hipSuccess) return err;
             continue;
         }
@@ -565,63 +570,31 @@ hipError_t launch_fused3d_batch_cfg(const PassArgs *ps, int n, BatchStaging *sta
         jobs.push_back(a);
         start.push_back(start.back() + a.ntiles);
     }
-    if (jobs.empty()) return hipSuccess;
     void *djobs = nullptr, *dstart = nullptr;
     hipError_t e = stage_job_table(stage, jobs.data(), jobs.size() * sizeof(Args), start, &djobs, &dstart,
                                    stream);
+    if (e == hipSuccess) e = rows3d_allow_lds<Cfg>(kernel, pick.nw);
     if (e != hipSuccess) return e;
-    const int total = start.back();
-    hipLaunchKernelGGL((fused3d_batch_kernel<TS, TC, SHAPE, R, T, W, WY, TX, TY>),
-                       dim3(total < slots ? total : slots), dim3(TX * TY), 0, stream,
+    const int total = start.back(), slots = cus * occ.occ[pick.nw == kRowsMaxWaves];
+    hipLaunchKernelGGL(kernel, dim3(total < slots ? total : slots), dim3(64 * pick.nw), Cfg::lds_bytes(pick.nw), stream,
                        static_cast<const Args *>(djobs), static_cast<const int *>(dstart), (int)jobs.size());
     return hipGetLastError();
 }
 
-// Thread layouts: W consecutive columns per thread (float64 2, float32 4), 2
-// rows per thread.  Stars take 16 x 32 threads (a 64-row layout: the skirt is
-// a smaller share of it); measured on 512^3 against 16 x 16, Star-3D2R float32
-// T = 3 runs at 959 vs 517 GSt/s and Star-3D3R float64 T = 2 at 323 vs 281.
-// The 27-point box takes a 32-row x 64-column layout: 16 x 16 threads in
-// float32 (Box-3D1R T = 2: 601 vs 574 GSt/s with 32 thread rows; two resident
-// workgroups per CU matter more than a smaller skirt), 32 x 16 in float64
-// (406 vs 374 against 16 x 16: 512 columns take 9 output tiles of 60 instead
-// of 19 of 28).
-template <typename TS, int SHAPE, int R, int T>
-struct Fused3DShape {
-    static constexpr int W = sizeof(TS) == 8 ? 2 : 4;
-    static constexpr int WY = 2;
-    static constexpr int TX = SHAPE == STENCIL_STAR ? 16 : 64 / W;
-    static constexpr int TY = SHAPE == STENCIL_STAR ? 32 : 16;
-};
-
-template <typename TS, typename TC, int SHAPE, int R, int T>
-hipError_t launch_fused3d(const PassArgs &p, hipStream_t stream)
-{
-    using S = Fused3DShape<TS, SHAPE, R, T>;
-    return launch_fused3d_cfg<TS, TC, SHAPE, R, T, S::W, S::WY, S::TX, S::TY>(p, stream);
-}
-
-template <typename TS, typename TC, int SHAPE, int R, int T>
-hipError_t launch_fused3d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
-{
-    using S = Fused3DShape<TS, SHAPE, R, T>;
-    return launch_fused3d_batch_cfg<TS, TC, SHAPE, R, T, S::W, S::WY, S::TX, S::TY>(ps, n, stage, stream);
-}
-
-#define F3(TS, TC, DT, SH, R, T) \
-    {STENCIL_PATH_VALU, DT, SH, 3, R, T, &launch_fused3d<TS, TC, SH, R, T>, &launch_fused3d_batch<TS, TC, SH, R, T>}
-#define F3_S(TS, TC, DT)                                                                                  \
-    F3(TS, TC, DT, STENCIL_STAR, 1, 2), F3(TS, TC, DT, STENCIL_STAR, 1, 3), F3(TS, TC, DT, STENCIL_STAR, 2, 2), \
-        F3(TS, TC, DT, STENCIL_STAR, 2, 3), F3(TS, TC, DT, STENCIL_STAR, 3, 2), F3(TS, TC, DT, STENCIL_BOX, 1, 2), \
-        F3(TS, TC, DT, STENCIL_BOX, 1, 3)
+#define F3(TC, DT, SH, R, T) \
+    {STENCIL_PATH_VALU, DT, SH, 3, R, T, &launch_fused3d<TC, SH, R, T>, &launch_fused3d_batch<TC, SH, R, T>}
+#define F3_S(TC, DT)                                                                                  \
+    F3(TC, DT, STENCIL_STAR, 1, 2), F3(TC, DT, STENCIL_STAR, 1, 3), F3(TC, DT, STENCIL_STAR, 2, 2),   \
+        F3(TC, DT, STENCIL_STAR, 2, 3), F3(TC, DT, STENCIL_STAR, 3, 2), F3(TC, DT, STENCIL_BOX, 1, 2), \
+        F3(TC, DT, STENCIL_BOX, 1, 3)
 
 }  // namespace
 
 const std::vector<KernelEntry> &valu3d_fused_kernels()
 {
     static const std::vector<KernelEntry> table = {
-        F3_S(double, double, STENCIL_F64),
-        F3_S(float, float, STENCIL_F32),
+        F3_S(double, STENCIL_F64),
+        F3_S(float, STENCIL_F32),
     };
     return table;
 }

@@ -1,0 +1,69 @@
+"""Fused 3D passes at the edges of their tiles: 64-column layouts less a skirt
+of r*T columns per side, 4 or 8 waves of 4-6 rows less r*(T-1) rows per side,
+segments from a few planes (small grids) up.  Tolerances as for the other VALU
+kernels: FP64 relative max-norm error <= 1e-12, FP32 <= 1e-5."""
+import numpy as np
+import pytest
+
+from gpu_util import case_inputs, oracle, rel_inf, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-12, "f32": 1e-5}
+VARIANTS = [("star", 1, 2), ("star", 1, 3), ("star", 2, 2), ("star", 2, 3), ("star", 3, 2), ("box", 1, 2),
+            ("box", 1, 3)]
+
+
+@pytest.fixture(scope="module")
+def stl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_00477_amd as stl
+    stl.lib()
+    return stl
+
+
+def edge_dims(r, T):
+    """One tile exactly, one column / row more, fewer points than the skirt,
+    and one plane only."""
+    bx = 64 - 2 * r * T
+    return [(7, 30, bx), (12, 33, bx + 1), (1, 3, 2 * bx - 1), (40, 2, 5), (2, 77, 130), (65, 64, 64)]
+
+
+@pytest.mark.parametrize("shape,r,T", VARIANTS)
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("boundary", ["dirichlet", "periodic"])
+def test_fused3d_tile_edges(stl, shape, r, T, dt, boundary):
+    for dims in edge_dims(r, T):
+        u0, u0r, t, w = case_inputs(shape, 3, r, dims, dt, seed=6100 + 10 * r + T + sum(dims))
+        for rows in (None, 5):  # planes per segment: chosen, and fixed with a ragged last one
+            p = stl.Plan(shape, 3, r, w, dims, T=T, dtype=dt, path="valu", boundary=boundary, halo=0.5,
+                         tile_rows=rows)
+            got = run_gpu(p, t, T)
+            ref = oracle(shape, 3, r, w, u0, T, boundary, 0.5)
+            assert rel_inf(got, ref) <= TOL[dt], (dims, rows)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_fused3d_batch_of_uneven_grids(stl, dt):
+    """A batched launch picks its waves and segments for the whole list: each
+    result equals the grid swept alone, bit for bit."""
+    import torch
+    dims = [(97, 97, 97), (3, 5, 7), (64, 20, 131), (1, 61, 60), (30, 200, 200)]
+    for shape, r, T in VARIANTS:
+        plans, ins, outs, alone = [], [], [], []
+        for k, d in enumerate(dims):
+            u0, u0r, t, w = case_inputs(shape, 3, r, d, dt, seed=6300 + k)
+            plans.append(stl.Plan(shape, 3, r, w, d, T=T, dtype=dt, path="valu",
+                                  boundary="periodic" if k % 2 else "dirichlet", halo=0.25))
+            ins.append(t.cuda())
+            outs.append(torch.empty_like(ins[-1]))
+            alone.append(torch.empty_like(ins[-1]))
+        stl.run_batch(plans, ins, outs, [T] * len(dims))
+        for p, x, y in zip(plans, ins, alone):
+            p.run(x, y, T)
+        torch.cuda.synchronize()
+        for k in range(len(dims)):
+            assert torch.equal(outs[k], alone[k]), (shape, r, T, dims[k])
+            assert np.isfinite(outs[k].cpu().numpy()).all()
