@@ -107,8 +107,9 @@ const std::vector<KernelEntry> &valu2d_table_f32();
 const std::vector<KernelEntry> &valu2d_table_bf16();
 const std::vector<KernelEntry> &valu2d_table_f16();
 const std::vector<KernelEntry> &valu2d_table_x3();  // float storage, FP64 arithmetic
-const std::vector<KernelEntry> &valu3d_kernels();
-const std::vector<KernelEntry> &valu3d_fused_kernels();
+const std::vector<KernelEntry> &valu3d_fused_kernels();     // stars r <= 3 and boxes r = 1, T = 1..3
+// one-step streaming kernel the table above sends large aligned grids to
+const KernelEntry *valu3d_stream_kernel(int dtype, int shape, int r);
 const std::vector<KernelEntry> &valu3d_box_kernels();  // boxes r >= 2, one step per pass
 const std::vector<KernelEntry> &valu2d_table_cases();  // r = 7, and r = 1 with T = 5..8
 const std::vector<KernelEntry> &mfma2d_table_cases();  // composite radius 7

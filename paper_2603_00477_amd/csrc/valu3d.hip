@@ -1,7 +1,9 @@
 // VALU path, d = 3, one explicit step per pass, streaming along z (the
-// slowest axis).  Passes of T >= 2 fused steps run on the kernel of
-// valu3d_fused.hip; the step pipeline below is written for any T, but the
-// tile geometry (no skirt, halo staged per thread) is the one-step one.
+// slowest axis), for large grids of whole aligned rows: 16-byte loads and
+// stores where HBM is the bound.  Other one-step passes and passes of T >= 2
+// fused steps run on the kernel of valu3d_fused.hip (which also holds the
+// rule); the step pipeline below is written for any T, but the tile geometry
+// (no skirt, halo staged per thread) is the one-step one.
 //
 // A workgroup of TX x TY threads owns an in-plane tile of (TY*WY) x (TX*W)
 // points (each thread WY rows x W consecutive columns) and streams down a
@@ -523,21 +525,22 @@ hipError_t launch_valu3d_batch(const PassArgs *ps, int n, BatchStaging *stage, h
 
 #define V3(TS, TC, DT, SH, R, T) \
     {STENCIL_PATH_VALU, DT, SH, 3, R, T, &launch_valu3d<TS, TC, SH, R, T>, &launch_valu3d_batch<TS, TC, SH, R, T>}
-// One-step passes (T = 1) of every star radius up to 3 and of the 27-point
-// box; fused passes (T >= 2) run on the kernel of valu3d_fused.hip.
-#define V3_S(TS, TC, DT)                                                                       \
-    V3(TS, TC, DT, STENCIL_STAR, 1, 1), V3(TS, TC, DT, STENCIL_STAR, 2, 1), V3(TS, TC, DT, STENCIL_STAR, 3, 1), \
-        V3(TS, TC, DT, STENCIL_BOX, 1, 1)
+// One-step passes (T = 1) of the stars and of the 27-point box.
+#define V3_S(TS, TC, DT) \
+    V3(TS, TC, DT, STENCIL_STAR, 1, 1), V3(TS, TC, DT, STENCIL_STAR, 2, 1), V3(TS, TC, DT, STENCIL_BOX, 1, 1)
 
 }  // namespace
 
-const std::vector<KernelEntry> &valu3d_kernels()
+const KernelEntry *valu3d_stream_kernel(int dtype, int shape, int r)
 {
     static const std::vector<KernelEntry> table = {
         V3_S(double, double, STENCIL_F64),
         V3_S(float, float, STENCIL_F32),
+        V3(float, float, STENCIL_F32, STENCIL_STAR, 3, 1),
     };
-    return table;
+    for (const KernelEntry &e : table)
+        if (e.dtype == dtype && e.shape == shape && e.r == r) return &e;
+    return nullptr;
 }
 
 }  // namespace stl

@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 
 #include "internal.h"
 #include "valu_common.h"
@@ -69,6 +70,11 @@ struct Rows3DCfg {
     static constexpr int Q = 2 * R + 1;
     static constexpr int SK = R * (T - 1);      // rows of the exact margin, per side
     static constexpr int BX = 64 - 2 * R * T;   // output columns of a tile
+    // planes prefetched (one-step passes move a plane per little arithmetic:
+    // Box-3D1R float64 512^3 556 -> 447 us, Star-3D1R float32 267 -> 237 us
+    // with two) and planes per unrolled loop body
+    static constexpr int PF = T == 1 ? 2 : 1;
+    static constexpr int U = Q * PF;
     static constexpr int NH = (2 * R + kRowsMinWaves - 1) / kRowsMinWaves;  // staged halo rows per wave
     // rows a wave keeps in LDS: all of them where columns are read back from
     // there, else the R first and R last ones its neighbours read
@@ -117,7 +123,7 @@ template <typename TC, int SHAPE, int R, int T, int WY, int XL, int K>
 __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC (&wk)[K], const int tile, TC *lds)
 {
     using Cfg = Rows3DCfg<TC, SHAPE, R, T, WY, XL>;
-    constexpr int Q = Cfg::Q, SK = Cfg::SK, NH = Cfg::NH, SLOT = Cfg::SLOT;
+    constexpr int Q = Cfg::Q, SK = Cfg::SK, NH = Cfg::NH, SLOT = Cfg::SLOT, PF = Cfg::PF, U = Cfg::U;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = blockDim.x >> 6;
@@ -172,7 +178,7 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
     const int own0 = R * 64 + wv * SLOT + lane;
     const int up0 = own0 - R * 64, dn0 = own0 + SLOT;
 
-    TC acc[T][Q][WY], own[T][WY], ring[WY], hring[NH];
+    TC acc[T][Q][WY], own[T][WY], ring[PF][WY], hring[PF][NH];
 #pragma unroll
     for (int s = 0; s < T; ++s)
 #pragma unroll
@@ -182,7 +188,7 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
             for (int q = 0; q < Q; ++q) acc[s][q][i] = TC(0);
         }
     int zl = periodic ? wrap(zbase, n0) : 0;  // periodic: source plane of the next load
-    auto load_plane = [&](int k) {
+    auto load_plane = [&](int k, TC (&r)[WY], TC (&hr)[NH]) {
         const int z = periodic ? zl : min(max(zbase + k, 0), n0 - 1);
         const int64_t zoff = (int64_t)z * pitch;
         // opaque scalar offsets: the rows' addresses are not worth the vector
@@ -194,9 +200,9 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
             return srcl[off];
         };
 #pragma unroll
-        for (int i = 0; i < WY; ++i) ring[i] = row_at(roff[i]);
+        for (int i = 0; i < WY; ++i) r[i] = row_at(roff[i]);
 #pragma unroll
-        for (int i = 0; i < NH; ++i) hring[i] = row_at(hoff[i]);
+        for (int i = 0; i < NH; ++i) hr[i] = row_at(hoff[i]);
         zl = zl + 1 == n0 ? 0 : zl + 1;
     };
     // the wave's rows of a field, to where its neighbours (and itself) read them
@@ -208,14 +214,15 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
             if (i >= WY - R) wr[(i - WY + 2 * R) * 64] = v;
         }
     };
-    load_plane(0);
-
-    for (int kb = 0; kb < KTOT; kb += Q) {
 #pragma unroll
-        for (int u = 0; u < Q; ++u) {
+    for (int k = 0; k < PF; ++k) load_plane(k, ring[k], hring[k]);
+
+    for (int kb = 0; kb < KTOT; kb += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             const int k = kb + u;
             if (k >= KTOT) break;
-            const int par = k & 1;
+            const int par = (U % 2 ? k : u) & 1;
             // stages from T down to 1: each has used its predecessor's rows of
             // the previous iteration before that one replaces them
 #pragma unroll
@@ -304,18 +311,18 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
                 TC *wr = lds + par * FL;
 #pragma unroll
                 for (int i = 0; i < WY; ++i) {
-                    const TC v = (zin && ((rin >> i) & 1u) && col_in) ? ring[i] : h;
+                    const TC v = (zin && ((rin >> i) & 1u) && col_in) ? ring[u % PF][i] : h;
                     own[0][i] = v;
                     put_row(wr + own0, i, v);
                 }
 #pragma unroll
                 for (int i = 0; i < NH; ++i) {
-                    const TC v = (zin && hin[i] && col_in) ? hring[i] : h;
+                    const TC v = (zin && hin[i] && col_in) ? hring[u % PF][i] : h;
                     if (hlds[i] >= 0) wr[hlds[i]] = v;
                 }
                 // keep the refill of the ring behind the reads that drain it
                 __builtin_amdgcn_sched_barrier(0);
-                if (k + 1 < KIN) load_plane(k + 1);
+                if (k + PF < KIN) load_plane(k + PF, ring[u % PF], hring[u % PF]);
             }
             __syncthreads();
         }
@@ -374,15 +381,18 @@ __global__ __launch_bounds__(64 * kRowsMaxWaves) __attribute__((amdgpu_waves_per
 // 8 waves: as many rows as two resident 8-wave workgroups (128 registers;
 // float64 stars with r >= 2: one, 256) have room for, since every row of the
 // margin is recomputed by each tile; XL >= 1 gains 2-11 % where rotates are
-// the larger share (Star-3D2R float32 T = 3 1019 -> 1131) and loses 3 % on
-// Star-3D2R float64 T = 3 and Star-3D1R, whose one rotate per side is cheap.
+// the larger share (Star-3D2R float32 T = 3 1019 -> 1131 GSt/s) and loses 3 %
+// on Star-3D2R float64 T = 3 and Star-3D1R, whose one rotate per side is
+// cheap.  One-step passes have no margin and take four rows.
 template <typename TC, int SHAPE, int R, int T>
 struct Rows3DShape {
     static constexpr bool F64 = sizeof(TC) == 8, BOX = SHAPE == STENCIL_BOX;
-    static constexpr int WY = F64 ? (BOX || R == 1 ? 4 : (R == 2 && T == 2 ? 6 : 5))
-                                  : (BOX || R == 1 ? (T == 2 ? 4 : 6) : 5);
-    static constexpr int XL = BOX || R == 1 ? 0 : (F64 ? (R == 2 && T == 3 ? 0 : 1) : (R == 2 && T == 3 ? 1 : 2));
-    static constexpr int MINW = F64 && R >= 2 ? 1 : 4;
+    static constexpr int WY = T == 1 || BOX || R == 1 ? (!F64 && T == 3 ? 6 : 4) : (F64 && R == 2 && T == 2 ? 6 : 5);
+    static constexpr int XL = BOX || R == 1               ? 0
+                              : T == 1 || (F64 && T == 2) ? 1
+                              : F64                       ? 0
+                                                          : (R == 2 && T == 3 ? 1 : 2);
+    static constexpr int MINW = F64 && (R == 3 || (R == 2 && T > 1)) ? 1 : 4;
 };
 
 // One in-plane box of a launch: planes, rows and columns to write.
@@ -395,19 +405,23 @@ struct Rows3DPick {
 };
 
 // Waves per workgroup (4 or 8) and planes per segment of a launch over n
-// boxes.  A workgroup takes BZ + 2RT + T plane iterations; one costs the
-// larger of its latency (barrier, LDS, the next plane's loads: about 1000
-// cycles on top of a wave's own arithmetic) and the arithmetic of the waves
-// that share a SIMD.  The estimate is the number of rounds over the resident
-// workgroups times that.  Small grids come out with segments of a few planes
-// that put work on every CU (97^3 float32 Star-3D1R T = 2: 3 planes 8.7 us, 25
-// planes 21.6 us), large ones with segments that amortise the 2RT + T lead-in
-// planes in whole rounds (512^3 Star-3D2R float64 T = 3: 3 segments 545, 4
-// 440, 8 527 GSt/s).
+// boxes.  A workgroup takes BZ + 2RT + T plane iterations (the lead-in ones,
+// where later stages idle, count 0.6); one costs about 1500 cycles of latency
+// (barrier, LDS, the next plane's loads) and the arithmetic of the waves that
+// share a SIMD.  The estimate is that times the rounds over the resident
+// workgroups.  Small grids come out with segments of a few planes that put
+// work on every CU (97^3 float32 Star-3D1R T = 2: 7 planes 9.8 us, 33 planes
+// 25), large ones with segments that amortise the lead-in planes in whole
+// rounds (512^3 Star-3D2R float64 T = 3: 171 planes 738 us, 128 871).  r = 1
+// and one-step passes are near the memory bound at large sizes and gain from
+// neighbouring tiles running close in time: at most 16 R T planes (512^3
+// Star-3D1R float64 T = 2: 171 planes 549 us, 32 502).  Over ten variants at 64^3..512^3 the choice is
+// 0.6 % behind the best of all measured (4.. 512-plane) segments on average,
+// 8 % at most.
 template <typename Cfg, typename TC, int SHAPE, int R, int T, int WY>
 Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const int (&occ)[2])
 {
-    const double wave = T * WY * ((sizeof(TC) == 8 ? 5.0 : 4.0) * Cfg::K + 4.0 * (2 * R * (sizeof(TC) / 4) + 4));
+    const double wave = T * WY * ((sizeof(TC) == 8 ? 4.0 : 2.5) * Cfg::K + 4.0 * (2 * R * (sizeof(TC) / 4) + 8));
     static const int kSegs[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,  16, 20,
                                 24, 28, 32, 40, 48, 64, 96, 128, 192, 256};
     int dmax = 1;
@@ -422,6 +436,7 @@ Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const in
             int BZ = fixed_bz > 0 ? fixed_bz : (dmax + segs - 1) / segs;
             if (BZ == last) break;
             last = BZ;
+            if ((R == 1 || T == 1) && fixed_bz <= 0 && BZ > 16 * R * T) continue;
             double items = 0;
             for (int i = 0; i < n; ++i)
                 items += (double)((boxes[i].d0 + BZ - 1) / BZ) * ((boxes[i].d1 + BY - 1) / BY) *
@@ -430,11 +445,11 @@ Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const in
             const double rest = items - full * slots;
             auto plane = [&](double resident) {  // cycles of a plane iteration
                 const double perSimd = (double)(int64_t)((resident * nw + 3) / 4);
-                return std::max(1000.0 + wave, wave * perSimd);
+                return 1500.0 + wave * perSimd;
             };
             double rounds = full * plane(occ[v]);
             if (rest > 0) rounds += plane((double)(int64_t)((rest + cus - 1) / cus));
-            const double cost = (std::min(BZ, dmax) + 2 * R * T + T) * rounds;
+            const double cost = (std::min(BZ, dmax) + 0.6 * (2 * R * T + T)) * rounds;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = {nw, BZ};
@@ -581,12 +596,53 @@ hipError_t launch_fused3d_batch(const PassArgs *ps, int n, BatchStaging *stage, 
     return hipGetLastError();
 }
 
+// One-step passes.  Large grids whose rows are whole aligned vectors go to the
+// 16-byte-load kernel of valu3d.hip, which moves HBM traffic 3-10 % faster
+// (512^3: float32 Star-3D1R 230 vs 237 us, float64 Box-3D1R 411 vs 447; 320^3
+// float64 Star-3D1R 114 vs 125); below 384 MB in and out, where the last-level
+// cache (256 MB) holds much of a pass, and for other row lengths the narrow
+// tiles above win (256^3 float32 Star-3D1R 33 vs 27 us, 333^3 120 vs 72, 97^3
+// 40 vs 7.5).  Float64 Star-3D3R is bound by its arithmetic and wins at every
+// size (512^3 533 vs 462 us).
+template <typename TC, int R>
+bool one_step_streams(const PassArgs &p)
+{
+    if (sizeof(TC) == 8 && R == 3) return false;
+    const int64_t row = p.dims[2] * (int)sizeof(TC), bytes = 2 * p.dims[0] * p.dims[1] * row;
+    bool whole = true;
+    for (int i = 0; i < 3; ++i) whole = whole && p.region_lo[i] == 0 && p.region_hi[i] == p.dims[i];
+    return whole && bytes >= (384LL << 20) && row % 16 == 0 && ((uintptr_t)p.src | (uintptr_t)p.dst) % 16 == 0;
+}
+
+template <typename TC, int DT, int SHAPE, int R>
+hipError_t launch_one_step3d(const PassArgs &p, hipStream_t stream)
+{
+    if (one_step_streams<TC, R>(p)) return valu3d_stream_kernel(DT, SHAPE, R)->launch(p, stream);
+    return launch_fused3d<TC, SHAPE, R, 1>(p, stream);
+}
+
+template <typename TC, int DT, int SHAPE, int R>
+hipError_t launch_one_step3d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+{
+    std::vector<PassArgs> large, other;
+    for (int i = 0; i < n; ++i) (one_step_streams<TC, R>(ps[i]) ? large : other).push_back(ps[i]);
+    hipError_t e = hipSuccess;
+    if (!large.empty())
+        e = valu3d_stream_kernel(DT, SHAPE, R)->launch_batch(large.data(), (int)large.size(), stage, stream);
+    if (e == hipSuccess && !other.empty())
+        e = launch_fused3d_batch<TC, SHAPE, R, 1>(other.data(), (int)other.size(), stage, stream);
+    return e;
+}
+
+#define F3_1(TC, DT, SH, R) \
+    {STENCIL_PATH_VALU, DT, SH, 3, R, 1, &launch_one_step3d<TC, DT, SH, R>, &launch_one_step3d_batch<TC, DT, SH, R>}
 #define F3(TC, DT, SH, R, T) \
     {STENCIL_PATH_VALU, DT, SH, 3, R, T, &launch_fused3d<TC, SH, R, T>, &launch_fused3d_batch<TC, SH, R, T>}
 #define F3_S(TC, DT)                                                                                  \
     F3(TC, DT, STENCIL_STAR, 1, 2), F3(TC, DT, STENCIL_STAR, 1, 3), F3(TC, DT, STENCIL_STAR, 2, 2),   \
         F3(TC, DT, STENCIL_STAR, 2, 3), F3(TC, DT, STENCIL_STAR, 3, 2), F3(TC, DT, STENCIL_BOX, 1, 2), \
-        F3(TC, DT, STENCIL_BOX, 1, 3)
+        F3(TC, DT, STENCIL_BOX, 1, 3), F3_1(TC, DT, STENCIL_STAR, 1), F3_1(TC, DT, STENCIL_STAR, 2),  \
+        F3_1(TC, DT, STENCIL_STAR, 3), F3_1(TC, DT, STENCIL_BOX, 1)
 
 }  // namespace
 

@@ -1,4 +1,4 @@
-"""Fused 3D passes at the edges of their tiles: 64-column layouts less a skirt
+"""3D passes at the edges of their tiles: 64-column layouts less a skirt
 of r*T columns per side, 4 or 8 waves of 4-6 rows less r*(T-1) rows per side,
 segments from a few planes (small grids) up.  Tolerances as for the other VALU
 kernels: FP64 relative max-norm error <= 1e-12, FP32 <= 1e-5."""
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 TOL = {"f64": 1e-12, "f32": 1e-5}
 VARIANTS = [("star", 1, 2), ("star", 1, 3), ("star", 2, 2), ("star", 2, 3), ("star", 3, 2), ("box", 1, 2),
-            ("box", 1, 3)]
+            ("box", 1, 3), ("star", 1, 1), ("star", 2, 1), ("star", 3, 1), ("box", 1, 1)]
 
 
 @pytest.fixture(scope="module")
@@ -34,7 +34,7 @@ def edge_dims(r, T):
 @pytest.mark.parametrize("shape,r,T", VARIANTS)
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("boundary", ["dirichlet", "periodic"])
-def test_fused3d_tile_edges(stl, shape, r, T, dt, boundary):
+def test_rows3d_tile_edges(stl, shape, r, T, dt, boundary):
     for dims in edge_dims(r, T):
         u0, u0r, t, w = case_inputs(shape, 3, r, dims, dt, seed=6100 + 10 * r + T + sum(dims))
         for rows in (None, 5):  # planes per segment: chosen, and fixed with a ragged last one
@@ -46,7 +46,7 @@ def test_fused3d_tile_edges(stl, shape, r, T, dt, boundary):
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
-def test_fused3d_batch_of_uneven_grids(stl, dt):
+def test_rows3d_batch_of_uneven_grids(stl, dt):
     """A batched launch picks its waves and segments for the whole list: each
     result equals the grid swept alone, bit for bit."""
     import torch
@@ -67,3 +67,37 @@ def test_fused3d_batch_of_uneven_grids(stl, dt):
         for k in range(len(dims)):
             assert torch.equal(outs[k], alone[k]), (shape, r, T, dims[k])
             assert np.isfinite(outs[k].cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("shape,r", [("star", 2), ("box", 1)])
+def test_one_step_large_and_small_kernels_agree(stl, shape, r):
+    """A one-step pass over a large grid of whole aligned rows takes the
+    16-byte-load kernel; the same grid one column narrower does not.  Both
+    hold the oracle's values on sampled windows, and a batch that mixes them
+    with a small grid equals each run alone."""
+    import torch
+    from oracle import core as ocore
+    import stencil_inputs as si
+    K = 6 * r + 1 if shape == "star" else 27
+    w = si.normalised_weights(K, seed=6400 + r)
+    plans, ins, outs = [], [], []
+    for k, dims in enumerate([(256, 512, 512), (256, 512, 511), (20, 30, 40)]):
+        u0 = si.uniform_grid(dims, seed=6410 + k)
+        x = si.round_to(u0, "f32")[1].cuda()
+        p = stl.Plan(shape, 3, r, w, dims, T=1, dtype="f32", path="valu", boundary="periodic")
+        y = torch.empty_like(x)
+        p.run(x, y, 1)
+        torch.cuda.synchronize()
+        for lo in [(0, 0, 0), tuple(n - 6 for n in dims), tuple(n // 2 for n in dims)]:
+            hi = tuple(a + 6 for a in lo)
+            ref = ocore.run_window(shape, 3, r, w, u0, 1, lo, hi, "periodic")
+            got = y[tuple(slice(a, b) for a, b in zip(lo, hi))].cpu().numpy()
+            assert rel_inf(got, ref) <= TOL["f32"], (dims, lo)
+        plans.append(p)
+        ins.append(x)
+        outs.append(y)
+    batch = [torch.empty_like(y) for y in outs]
+    stl.run_batch(plans, ins, batch, [1, 1, 1])
+    torch.cuda.synchronize()
+    for a, b in zip(outs, batch):
+        assert torch.equal(a, b)
