@@ -29,6 +29,7 @@
 // Contributions to one output arrive in canonical order (c, then a, then b
 // ascending), as in the oracle.
 
+#include <algorithm>
 #include <cstddef>
 #include <vector>
 
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(TX *TY) void valu3d_box_batch_kernel(
 }
 
 template <typename TS, typename TC, int R, int W, int WY, int TX, int TY>
-bool box3_args(const PassArgs &p, Box3Args<TC, Box3Cfg<TS, TC, R, W, WY, TX, TY>::K> *out, hipError_t *err)
+bool box3_args(const PassArgs &p, int BZ, Box3Args<TC, Box3Cfg<TS, TC, R, W, WY, TX, TY>::K> *out, hipError_t *err)
 {
     using Cfg = Box3Cfg<TS, TC, R, W, WY, TX, TY>;
     *err = hipSuccess;
@@ -333,25 +334,70 @@ bool box3_args(const PassArgs &p, Box3Args<TC, Box3Cfg<TS, TC, R, W, WY, TX, TY>
     }
     a.nty = (D1 + Cfg::BY - 1) / Cfg::BY;
     a.ntx = (D2 + Cfg::BX - 1) / Cfg::BX;
-    int BZ = p.tile_rows;
-    if (BZ <= 0) {
-        // about one resident set of workgroups, segments no shorter than 4R
-        // planes (the 2R halo planes of a segment cost (BZ + 2R) / BZ)
-        const int target = 4 * (p.num_cu > 0 ? p.num_cu : 256);
-        const int inplane = a.nty * a.ntx;
-        const int segs = (target + inplane - 1) / inplane;
-        BZ = (D0 + segs - 1) / segs;
-        if (BZ < 4 * R) BZ = 4 * R;
-    }
-    a.BZ = BZ;
-    a.nzs = (D0 + BZ - 1) / BZ;
-    const int64_t nt = (int64_t)a.nzs * a.nty * a.ntx;
-    if (nt > (1LL << 30)) {
+    const int64_t inplane = (int64_t)a.nty * a.ntx, most = 1LL << 30;
+    int64_t segs = (D0 + BZ - 1) / BZ;
+    if (p.tile_rows <= 0) segs = std::max<int64_t>(1, std::min(segs, most / inplane));
+    if (segs * inplane > most) {
         *err = hipErrorInvalidValue;
         return false;
     }
-    a.ntiles = (int)nt;
+    a.BZ = p.tile_rows > 0 ? p.tile_rows : (int)((D0 + segs - 1) / segs);
+    a.nzs = (D0 + a.BZ - 1) / a.BZ;
+    a.ntiles = (int)(a.nzs * inplane);
     return true;
+}
+
+// Planes per segment of a launch over n passes.  A workgroup takes BZ + 2R
+// plane iterations; one costs a latency that grows with the weight stream
+// (about 2000 cycles for 125 weights) and the FMAs of the waves that share a
+// SIMD.  The estimate is that times the rounds over the resident workgroups.
+// Measured at 64^3..512^3 against every length from 4 planes up, the choice is
+// 0.6 % behind the best on average, 3 % at most; a fixed target of four
+// workgroups per CU and at least 4R planes had been up to 43 % behind
+// (float32 Box-3D2R 64^3 34.5 -> 23.3, 200^3 67.5 -> 57.9 us with the tiles
+// below; Box-3D3R 64^3 78 -> 45, 200^3 200 -> 163).
+template <typename TC, int R, int W, int WY, int TX, int TY>
+int box3_segment(const PassArgs *ps, int n, int slots_per_cu, int cus)
+{
+    using Cfg = Box3Cfg<TC, TC, R, W, WY, TX, TY>;
+    static const int kSegs[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,  16, 20,
+                                24, 28, 32, 40, 48, 64, 96, 128, 192, 256};
+    const double wave = (sizeof(TC) == 8 ? 4.0 : 3.0) * Cfg::K * W * WY;
+    const double latency = 2000.0 * (R == 2 ? 1.0 : 2.0);
+    const int nw = TX * TY / 64, slots = cus * slots_per_cu;
+    auto extent = [](const PassArgs &p, int i) { return std::max(p.region_hi[i] - p.region_lo[i], 0); };
+    int dmax = 1;
+    for (int i = 0; i < n; ++i) dmax = std::max(dmax, extent(ps[i], 0));
+    int best = dmax, last = 0;
+    double best_cost = -1.0;
+    for (int segs : kSegs) {
+        const int BZ = (dmax + segs - 1) / segs;
+        if (BZ == last) break;
+        last = BZ;
+        double items = 0;
+        for (int i = 0; i < n; ++i)
+            items += (double)((extent(ps[i], 0) + BZ - 1) / BZ) * ((extent(ps[i], 1) + Cfg::BY - 1) / Cfg::BY) *
+                     ((extent(ps[i], 2) + Cfg::BX - 1) / Cfg::BX);
+        const double full = (double)(int64_t)(items / slots), rest = items - full * slots;
+        auto plane = [&](double resident) { return latency + wave * (double)(int64_t)((resident * nw + 3) / 4); };
+        double rounds = full * plane(slots_per_cu);
+        if (rest > 0) rounds += plane((double)(int64_t)((rest + cus - 1) / cus));
+        const double cost = (BZ + 1.6 * R) * rounds;
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = BZ;
+        }
+    }
+    return best;
+}
+
+// resident workgroups per CU
+template <typename K>
+int box3_occupancy(K kernel, int threads)
+{
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1) occ = 1;
+    return occ;
 }
 
 template <typename TS, typename TC, int R, int W, int WY, int TX, int TY>
@@ -359,9 +405,13 @@ hipError_t launch_box3_cfg(const PassArgs &p, hipStream_t stream)
 {
     using Cfg = Box3Cfg<TS, TC, R, W, WY, TX, TY>;
     static_assert(sizeof(Box3Args<TC, Cfg::K>) <= 4096, "weights exceed the kernel-argument block");
+    static const int occ = box3_occupancy(valu3d_box_kernel<TS, TC, R, W, WY, TX, TY>, TX * TY);
+    const int BZ = p.tile_rows > 0
+                       ? p.tile_rows
+                       : box3_segment<TC, R, W, WY, TX, TY>(&p, 1, occ, p.num_cu > 0 ? p.num_cu : 256);
     Box3Args<TC, Cfg::K> a;
     hipError_t err;
-    if (!box3_args<TS, TC, R, W, WY, TX, TY>(p, &a, &err)) return err;
+    if (!box3_args<TS, TC, R, W, WY, TX, TY>(p, BZ, &a, &err)) return err;
     hipLaunchKernelGGL((valu3d_box_kernel<TS, TC, R, W, WY, TX, TY>), dim3(a.ntiles), dim3(TX * TY), 0,
                        stream, a);
     return hipGetLastError();
@@ -372,13 +422,16 @@ hipError_t launch_box3_batch_cfg(const PassArgs *ps, int n, BatchStaging *stage,
 {
     using Cfg = Box3Cfg<TS, TC, R, W, WY, TX, TY>;
     using Args = Box3Args<TC, Cfg::K>;
+    static const int occ = box3_occupancy(valu3d_box_batch_kernel<TS, TC, R, W, WY, TX, TY>, TX * TY);
+    const int cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
+    const int BZ = box3_segment<TC, R, W, WY, TX, TY>(ps, n, occ, cus);
     std::vector<Args> jobs;
     std::vector<int> start(1, 0);
     jobs.reserve(n);
     for (int i = 0; i < n; ++i) {
         Args a;
         hipError_t err;
-        if (!box3_args<TS, TC, R, W, WY, TX, TY>(ps[i], &a, &err)) {
+        if (!box3_args<TS, TC, R, W, WY, TX, TY>(ps[i], ps[i].tile_rows > 0 ? ps[i].tile_rows : BZ, &a, &err)) {
             if (err != hipSuccess) return err;
             continue;
         }
@@ -391,11 +444,7 @@ hipError_t launch_box3_batch_cfg(const PassArgs *ps, int n, BatchStaging *stage,
     hipError_t e = stage_job_table(stage, jobs.data(), jobs.size() * sizeof(Args), start, &djobs, &dstart,
                                    stream);
     if (e != hipSuccess) return e;
-    int occ = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, valu3d_box_batch_kernel<TS, TC, R, W, WY, TX, TY>,
-                                                     TX * TY, 0);
-    if (e != hipSuccess || occ < 1) occ = 1;
-    const int slots = occ * (ps[0].num_cu > 0 ? ps[0].num_cu : 256);
+    const int slots = occ * cus;
     const int total = start.back();
     hipLaunchKernelGGL((valu3d_box_batch_kernel<TS, TC, R, W, WY, TX, TY>), dim3(total < slots ? total : slots),
                        dim3(TX * TY), 0, stream, static_cast<const Args *>(djobs),
@@ -403,24 +452,56 @@ hipError_t launch_box3_batch_cfg(const PassArgs *ps, int n, BatchStaging *stage,
     return hipGetLastError();
 }
 
-// Tiles: 16 columns of threads with one 16-byte vector each (float32 4
-// points, float64 2) and one row per thread; 16 thread rows for r = 3, 32 for
-// r = 2.  Measured on 384^3 / 512^3 periodic grids against 2-row threads,
-// 3-row threads and 8 x 32 / 32 x 8 thread tiles: the one-row threads need
-// 70-96 VGPRs and keep 5-7 waves per SIMD, which hides the LDS and
-// scalar-load latencies best (5-15 % faster).
+// Tiles: one 16-byte vector (float32 4 points, float64 2) and one row per
+// thread, 32 columns of points: 8 x 32 threads in float32, 16 x 16 in float64.
+// Measured on 384^3 / 512^3 periodic grids against 2-row and 3-row threads, the
+// one-row threads need 70-96 VGPRs and keep 5-7 waves per SIMD, which hides
+// the LDS and scalar-load latencies best (5-15 % faster).  Against 64-column
+// tiles (16 x 32 and 16 x 16 threads in float32, 16 x 32 in float64), each with
+// its best segments, the 32-column ones waste less of the last tile and
+// balance finer: Box-3D2R float32 200^3 65.9 -> 57.9 us, 512^3 470 -> 461;
+// Box-3D3R float32 200^3 184 -> 163; Box-3D2R float64 512^3 701 -> 671.
+template <typename TC, int R>
+struct Box3Shape {
+    static constexpr int W = sizeof(TC) == 8 ? 2 : 4;
+    static constexpr int TX = sizeof(TC) == 8 ? 16 : 8;
+    static constexpr int TY = sizeof(TC) == 8 ? 16 : 32;
+};
+
+// Float32 r = 2 grids of up to 160^3 points go to the row kernel of
+// valu3d_fused.hip, whose 125 weights stay in vector registers: with one wave
+// per SIMD the weight stream's latency is the bound here (Box-3D2R 64^3 23.3
+// vs 14.0 us, 97^3 32.7 vs 18.6, 160^3 36.8 vs 31.5; 200^3 57.9 vs 60.2,
+// 256^3 80 vs 95).
+template <typename TC, int R>
+bool box3_small(const PassArgs &p)
+{
+    if (sizeof(TC) != 4 || R != 2) return false;
+    int64_t points = 1;
+    for (int i = 0; i < 3; ++i) points *= std::max(p.region_hi[i] - p.region_lo[i], 0);
+    return points <= (int64_t)160 * 160 * 160;
+}
+
 template <typename TS, typename TC, int R>
 hipError_t launch_box3(const PassArgs &p, hipStream_t stream)
 {
-    constexpr int W = sizeof(TC) == 8 ? 2 : 4;
-    return launch_box3_cfg<TS, TC, R, W, 1, 16, (R >= 3 ? 16 : 32)>(p, stream);
+    using S = Box3Shape<TC, R>;
+    if (box3_small<TC, R>(p)) return rows3d_box2_kernel().launch(p, stream);
+    return launch_box3_cfg<TS, TC, R, S::W, 1, S::TX, S::TY>(p, stream);
 }
 
 template <typename TS, typename TC, int R>
 hipError_t launch_box3_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    constexpr int W = sizeof(TC) == 8 ? 2 : 4;
-    return launch_box3_batch_cfg<TS, TC, R, W, 1, 16, (R >= 3 ? 16 : 32)>(ps, n, stage, stream);
+    using S = Box3Shape<TC, R>;
+    std::vector<PassArgs> small, other;
+    for (int i = 0; i < n; ++i) (box3_small<TC, R>(ps[i]) ? small : other).push_back(ps[i]);
+    hipError_t e = hipSuccess;
+    if (!other.empty())
+        e = launch_box3_batch_cfg<TS, TC, R, S::W, 1, S::TX, S::TY>(other.data(), (int)other.size(), stage, stream);
+    if (e == hipSuccess && !small.empty())
+        e = rows3d_box2_kernel().launch_batch(small.data(), (int)small.size(), stage, stream);
+    return e;
 }
 
 #define B3(TS, TC, DT, R) \

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 TOL = {"f64": 1e-12, "f32": 1e-5}
 VARIANTS = [("star", 1, 2), ("star", 1, 3), ("star", 2, 2), ("star", 2, 3), ("star", 3, 2), ("box", 1, 2),
-            ("box", 1, 3), ("star", 1, 1), ("star", 2, 1), ("star", 3, 1), ("box", 1, 1)]
+            ("box", 1, 3), ("star", 1, 1), ("star", 2, 1), ("star", 3, 1), ("box", 1, 1), ("box", 2, 1),
+            ("box", 3, 1)]
 
 
 @pytest.fixture(scope="module")
@@ -69,6 +70,39 @@ def test_rows3d_batch_of_uneven_grids(stl, dt):
             assert np.isfinite(outs[k].cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("r", [2, 3])
+def test_large_box_beyond_the_small_grid_rule(stl, dt, r):
+    """Boxes r >= 2 over 160^3 points (float32 r = 2 below that takes the row
+    kernel): ragged 32-column tiles and segments, sampled windows, and a batch
+    with a small grid."""
+    import torch
+    from oracle import core as ocore
+    import stencil_inputs as si
+    w = si.normalised_weights((2 * r + 1) ** 3, seed=6500 + r)
+    plans, ins, outs = [], [], []
+    for k, dims in enumerate([(161, 165, 163), (9, 40, 33)]):
+        u0 = si.uniform_grid(dims, seed=6510 + k)
+        x = si.round_to(u0, dt)[1].cuda()
+        p = stl.Plan("box", 3, r, w, dims, T=1, dtype=dt, path="valu", halo=0.25)
+        y = torch.empty_like(x)
+        p.run(x, y, 1)
+        torch.cuda.synchronize()
+        for lo in [(0, 0, 0), tuple(n - 6 for n in dims), tuple(min(n // 2, n - 6) for n in dims)]:
+            hi = tuple(a + 6 for a in lo)
+            ref = ocore.run_window("box", 3, r, w, u0, 1, lo, hi, "dirichlet", 0.25)
+            got = y[tuple(slice(a, b) for a, b in zip(lo, hi))].cpu().numpy()
+            assert rel_inf(got, ref) <= TOL[dt], (dims, lo)
+        plans.append(p)
+        ins.append(x)
+        outs.append(y)
+    batch = [torch.empty_like(y) for y in outs]
+    stl.run_batch(plans, ins, batch, [1, 1])
+    torch.cuda.synchronize()
+    for a, b in zip(outs, batch):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("shape,r", [("star", 2), ("box", 1)])
 def test_one_step_large_and_small_kernels_agree(stl, shape, r):
     """A one-step pass over a large grid of whole aligned rows takes the
@@ -88,7 +122,7 @@ def test_one_step_large_and_small_kernels_agree(stl, shape, r):
         y = torch.empty_like(x)
         p.run(x, y, 1)
         torch.cuda.synchronize()
-        for lo in [(0, 0, 0), tuple(n - 6 for n in dims), tuple(n // 2 for n in dims)]:
+        for lo in [(0, 0, 0), tuple(n - 6 for n in dims), tuple(min(n // 2, n - 6) for n in dims)]:
             hi = tuple(a + 6 for a in lo)
             ref = ocore.run_window(shape, 3, r, w, u0, 1, lo, hi, "periodic")
             got = y[tuple(slice(a, b) for a, b in zip(lo, hi))].cpu().numpy()
