@@ -31,7 +31,9 @@
 
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
+#include <vector>
 
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -50,6 +52,7 @@ struct Valu2DJob {
     int n0, n1;
     int oy0, oy1, ox0, ox1;
     int BX, BY, nbands, nsegs;
+    int anchor;  // first column of band 1 where bands are anchored to the right edge, else -1
     int nwg;  // workgroup items: ceil(nbands / waves) band groups x nsegs segments
     int periodic;
     TC h;
@@ -90,8 +93,10 @@ struct Valu2DCfg {
     // 32-byte lanes, which stream them too: each weight then serves four
     // columns, and the freed registers hold the wider accumulators at two
     // waves per SIMD.
+    // Single-column lanes hold few accumulators and keep them in registers
+    // (a streamed column would serve 2R+1 FMAs only), r = 7 excepted.
     static constexpr bool WPTR = SHAPE == STENCIL_BOX && sizeof(TC) * K > 192 &&
-                                 (T >= 3 || sizeof(TC) == 8 || sizeof(TC) * K > 512);
+                                 (W > 1 ? (T >= 3 || sizeof(TC) == 8 || sizeof(TC) * K > 512) : R >= 7);
     // Streamed weights at T >= 3: each column is fetched once per input row
     // and serves every stage (columns outer, stages inner) instead of once
     // per stage.  Measured on 8192^2: Box-2D2R float64 T = 4 476 -> 570,
@@ -144,8 +149,8 @@ template <bool PREV>
 __device__ __forceinline__ double lane_rotate(double v)
 {
     const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), PREV ? 0x13C : 0x134, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), PREV ? 0x13C : 0x134, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), PREV ? 0x13C : 0x134, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), PREV ? 0x13C : 0x134, 0xF, 0xF, true);
     return __longlong_as_double(((long long)(unsigned)lo) | ((long long)hi << 32));
 }
 
@@ -181,14 +186,7 @@ __device__ __forceinline__ void assemble_window(const TC (&own)[W], TC (&win)[W 
 }
 
 // One tile (column band x row segment) of one pass, run by one wave.
-// FAST: the grid rows are whole aligned vectors and the output box starts on
-// a vector boundary, so every lane's W columns lie wholly inside or wholly
-// outside the grid.  Row loads are then one unconditional vector load per
-// row (periodic lanes and rows wrap by whole vectors; Dirichlet ones outside
-// the grid load a valid dummy and take h when the row is consumed); with no
-// other write to the prefetch ring, the compiler waits only for the row being
-// consumed and the loads of the next rows stay in flight.
-template <typename TS, typename TC, int SHAPE, int R, int T, int W, bool FAST>
+template <typename TS, typename TC, int SHAPE, int R, int T, int W>
 __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                                             const TC (&wk)[Valu2DCfg<TS, TC, SHAPE, R, T, W>::WPTR
                                                                ? 1
@@ -200,11 +198,11 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
     constexpr int U = Cfg::U;
     using Vec = RawVec<TS, W>;
 
-    const int x0 = a.ox0 + band * a.BX;
+    const int x0 = a.anchor >= 0 && band > 0 ? a.anchor + (band - 1) * a.BX : a.ox0 + band * a.BX;
     const int y0 = a.oy0 + seg * a.BY;
     const int y1 = min(y0 + a.BY, a.oy1);
     const int BYe = y1 - y0;
-    const int xe = min(x0 + a.BX, a.ox1);
+    const int xe = a.anchor >= 0 && band == 0 ? a.anchor : min(x0 + a.BX, a.ox1);
     const int cb = x0 - Cfg::E + lane * W;  // first column owned by this lane
 
     const TS *src = static_cast<const TS *>(a.src);
@@ -213,28 +211,24 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
     const bool periodic = a.periodic != 0;
     const TC h = a.h;
 
-    bool col_in[W];
-    int col_src[W];
-    bool col_store[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const int c = cb + j;
-        col_in[j] = c >= 0 && c < n1;
-        col_src[j] = periodic ? wrap(c, n1) : c;
-        col_store[j] = c >= x0 && c < xe;
-    }
-    const bool vec_ok = vec_aligned<TS, W>(src, n1, cb) && cb >= 0 && cb + W <= n1;
+    // The lane's columns lie wholly inside or wholly outside the grid (see
+    // valu2d_bands; W = 1 always does): its source column (wrapped, or a valid
+    // dummy) and whether a Dirichlet lane takes h instead.  Lanes of skirt
+    // columns that no output needs may straddle the edge: they load in bounds.
+    const bool lane_in = periodic || (cb >= 0 && cb + W <= n1);
+    const int f_col = lane_in ? min(wrap(cb, n1), max(n1 - W, 0)) : 0;
     // output stores: the whole vector, or (lanes at the band's ragged edge)
     // element by element; the element path is skipped by a wave-uniform
     // branch when no lane of the wave needs it
-    bool st_all = vec_ok, st_any = false;
+    bool col_store[W];
+    bool st_all = true, st_any = false;
 #pragma unroll
     for (int j = 0; j < W; ++j) {
+        col_store[j] = cb + j >= x0 && cb + j < xe;
         st_all = st_all && col_store[j];
         st_any = st_any || col_store[j];
     }
     const bool st_part_wave = __ballot(st_any && !st_all) != 0;
-    const TS hs = to_storage<TS>(h);
 
     const int KTOT = BYe + 2 * R * T + T;
     const int ybase = y0 - R * T;
@@ -254,41 +248,15 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
 #pragma unroll
         for (int j = 0; j < W + 2 * R; ++j) wins[s][j] = TC(0);
 
-    // fast path: the lane's source column (wrapped, or a valid dummy) and
-    // whether its vector lies outside a Dirichlet grid
-    int f_col = cb;
-    bool f_h = false;
-    if constexpr (FAST) {
-        if (periodic) {
-            f_col = wrap(cb, n1);
-        } else {
-            const bool in = cb >= 0 && cb + W <= n1;
-            f_h = !in;
-            f_col = in ? cb : 0;
-        }
-    }
+    // one unconditional vector load per row (rows wrap or clamp; those outside
+    // a Dirichlet grid are replaced by h when consumed): with no other write to
+    // the prefetch ring, the compiler waits only for the row being consumed
+    // and the loads of the next rows stay in flight
+    int rl = periodic ? wrap(ybase, n0) : 0;  // periodic: source row of the next load
     auto load_row = [&](int k, Vec &v) {
-        const int i = ybase + k;
-        if constexpr (FAST) {
-            const int ri = periodic ? wrap(i, n0) : min(max(i, 0), n0 - 1);
-            v.load(src + (int64_t)ri * n1 + f_col);
-            return;
-        }
-        const bool row_in = i >= 0 && i < n0;
-        if (!periodic && !row_in) {
-#pragma unroll
-            for (int j = 0; j < W; ++j) v.e[j] = hs;
-            return;
-        }
-        const int ri = periodic ? wrap(i, n0) : i;
-        const TS *rowp = src + (int64_t)ri * n1;
-        if (vec_ok) {
-            v.load(rowp + cb);
-        } else {
-#pragma unroll
-            for (int j = 0; j < W; ++j)
-                v.e[j] = (periodic || col_in[j]) ? rowp[col_src[j]] : hs;
-        }
+        const int ri = periodic ? rl : min(max(ybase + k, 0), n0 - 1);
+        v.load_any(src + (int64_t)ri * n1 + f_col);
+        rl = rl + 1 == n0 ? 0 : rl + 1;
     };
 
     constexpr int P = Cfg::P;
@@ -440,17 +408,17 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                     for (int j = 0; j < W; ++j) outv[j] = acc[s - 1][qc][j];
                     if (s < T) {
                         if (!periodic) {
-                            const bool row_in = yo >= 0 && yo < n0;
+                            const bool in = lane_in && yo >= 0 && yo < n0;
 #pragma unroll
                             for (int j = 0; j < W; ++j)
-                                if (!(row_in && col_in[j])) outv[j] = h;
+                                if (!in) outv[j] = h;
                         }
                     } else if (yo >= y0 && yo < y1) {
                         TS *rowp = dst + (int64_t)yo * n1;
                         Vec ov;
 #pragma unroll
                         for (int j = 0; j < W; ++j) ov.e[j] = to_storage<TS>(outv[j]);
-                        if (st_all) ov.store(rowp + cb);
+                        if (st_all) ov.store_any(rowp + cb);
                         if (st_part_wave && !st_all) {
 #pragma unroll
                             for (int j = 0; j < W; ++j)
@@ -466,15 +434,10 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
             // ---- stage 0: input row (window for stage 1), prefetch P rows ahead
             {
                 TC inrow[W];
-                if constexpr (FAST) {
-                    const int i = ybase + k;
-                    const bool hrow = f_h || (!periodic && (i < 0 || i >= n0));
+                const int i = ybase + k;
+                const bool hrow = !lane_in || (!periodic && (i < 0 || i >= n0));
 #pragma unroll
-                    for (int j = 0; j < W; ++j) inrow[j] = hrow ? h : to_compute<TC>(ring[u % P].e[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < W; ++j) inrow[j] = to_compute<TC>(ring[u % P].e[j]);
-                }
+                for (int j = 0; j < W; ++j) inrow[j] = hrow ? h : to_compute<TC>(ring[u % P].e[j]);
                 // keep the refill of this ring slot behind the reads that drain it
                 __builtin_amdgcn_sched_barrier(0);
                 if (k + P < KTOT) load_row(k + P, ring[u % P]);
@@ -502,11 +465,10 @@ __device__ __forceinline__ void load_weights(TC (&wk)[K], const SrcT *w)
     }
 }
 
-// Whether a job's tiles take the fast row loads (see valu2d_tile).
-template <typename TS, int W, typename TC>
-__device__ __forceinline__ bool valu2d_fast(const Valu2DJob<TC> &g)
+// Item of this wave in workgroup `wg` of a pass, the same for all its lanes.
+__device__ __forceinline__ int valu2d_item(int wg)
 {
-    return vec_aligned<TS, W>(g.src, g.n1, 0) && (g.ox0 % W) == 0;
+    return wg * kValu2DWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
 template <typename TS, typename TC, int SHAPE, int R, int T, int W>
@@ -514,14 +476,12 @@ __global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_kernel(
     Valu2DArgs<TC, Valu2DCfg<TS, TC, SHAPE, R, T, W>::K> a)
 {
     using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, W>;
-    // The waves of a workgroup take adjacent bands of one row segment (their
-    // skirt columns are read together); XCD-aware order: the workgroups
-    // resident on one XCD take consecutive segments of a band group (which
-    // share halo rows in that XCD's L2).
-    const int g = xcd_remap(blockIdx.x, gridDim.x);
-    if (g >= a.g.nwg) return;
-    const int band = (g / a.g.nsegs) * kValu2DWaves + (int)(threadIdx.x >> 6);
-    if (band >= a.g.nbands) return;
+    // Waves take (segment, band) items, bands fastest: adjacent bands share
+    // skirt columns in one CU's L1, and the contiguous run of items on an XCD
+    // shares halo rows in that XCD's L2.
+    const int item = valu2d_item(xcd_remap(blockIdx.x, gridDim.x));
+    if (item >= a.g.nbands * a.g.nsegs) return;
+    const int seg = item / a.g.nbands, band = item - seg * a.g.nbands;
     TC wk[Cfg::WPTR ? 1 : Cfg::K];
     ConstPtr<TC> wp = nullptr;
     if constexpr (Cfg::WPTR) {
@@ -534,10 +494,7 @@ __global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_kernel(
     } else {
         load_weights<TC, Cfg::K, SHAPE == STENCIL_STAR && R == 7>(wk, a.w);
     }
-    if (valu2d_fast<TS, W>(a.g))
-        valu2d_tile<TS, TC, SHAPE, R, T, W, true>(a.g, wk, wp, band, g % a.g.nsegs, threadIdx.x & 63);
-    else
-        valu2d_tile<TS, TC, SHAPE, R, T, W, false>(a.g, wk, wp, band, g % a.g.nsegs, threadIdx.x & 63);
+    valu2d_tile<TS, TC, SHAPE, R, T, W>(a.g, wk, wp, band, seg, threadIdx.x & 63);
 }
 
 // One job of a batched launch: geometry plus weights.
@@ -558,14 +515,14 @@ __global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_batch_kernel(
 {
     using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, W>;
     const int total = tile_start[njobs];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     int j = 0;
     for (int item = xcd_remap(blockIdx.x, gridDim.x); item < total; item += gridDim.x) {
         while (j + 1 < njobs && tile_start[j + 1] <= item) ++j;
         const Valu2DJob<TC> g = jobs[j].g;
-        const int local = item - tile_start[j];
-        const int band = (local / g.nsegs) * kValu2DWaves + wave;
-        if (band >= g.nbands) continue;
+        const int local = valu2d_item(item - tile_start[j]);
+        if (local >= g.nbands * g.nsegs) continue;
+        const int seg = local / g.nbands, band = local - seg * g.nbands;
         TC wk[Cfg::WPTR ? 1 : Cfg::K];
         ConstPtr<TC> wp = nullptr;
         if constexpr (Cfg::WPTR) {
@@ -574,34 +531,34 @@ __global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_batch_kernel(
         } else {
             load_weights<TC, Cfg::K, SHAPE == STENCIL_STAR && R == 7>(wk, jobs[j].w);
         }
-        if (valu2d_fast<TS, W>(g))
-            valu2d_tile<TS, TC, SHAPE, R, T, W, true>(g, wk, wp, band, local % g.nsegs, lane);
-        else
-            valu2d_tile<TS, TC, SHAPE, R, T, W, false>(g, wk, wp, band, local % g.nsegs, lane);
+        valu2d_tile<TS, TC, SHAPE, R, T, W>(g, wk, wp, band, seg, lane);
     }
 }
 
-// Columns per lane: one 16-byte vector, except float64 at T = 2, which takes
-// two (256-column bands: the 2E-column skirt is half the share of the band;
-// Box-2D3R 8192^2: 368 vs 345 GSt/s, Star-2D3R: 580 vs 528).  At T = 1 and
-// T >= 3 the 2-column lanes measured faster (occupancy), except for the
-// compute-bound float64 r = 7 passes, whose 8-column skirt is then half the
-// share of the band (10240^2 T = 1: Star-2D7R 260 -> 297, Box-2D7R 95 -> 101
-// GSt/s; memory-bound r <= 3 one-step passes 3-10 % slower with 4 columns).
-template <typename TS, int R, int T>
-struct Valu2DShape {
-    static constexpr int W = (sizeof(TS) == 8 && (T == 2 || (T == 1 && R >= 7)))
-                                 ? 4
-                                 : (16 / sizeof(TS) > 8 ? 8 : 16 / sizeof(TS));
-};
-
-// Fill the geometry of one pass; returns false when there is nothing to do.
-template <typename TS, typename TC, int SHAPE, int R, int T>
-bool valu2d_geometry(const PassArgs &p, Valu2DJob<TC> *g, hipError_t *err)
+// Columns per lane: 1, 2 or 4, picked per launch.  One-column lanes take any
+// grid and any box, put four times as many waves on a small grid and keep
+// large box weights in registers; four columns spend the smallest share on
+// skirts and window permutes.  Eight 16-bit columns measured slower than four
+// at every depth (8192^2 one step 55.9 vs 50.4 us, Star-2D2R T = 4 211 vs 120),
+// and float64 needs more registers than there are for four at T > 4.
+template <typename TC, int T>
+constexpr int valu2d_widest()
 {
-    using S = Valu2DShape<TS, R, T>;
-    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, S::W>;
-    *err = hipSuccess;
+    return sizeof(TC) == 8 && T > 4 ? 2 : 4;
+}
+
+// Column bands of a pass for W columns per lane; false where the lanes of a
+// band cannot all lie wholly inside or wholly outside the grid.  Rows of whole
+// vectors take bands from the box's first column on.  Rows of another length
+// put band 0 at the left edge and anchor the others to the right edge, so that
+// both edges fall between lanes (loads need no alignment beyond the element);
+// band 1 must start at least a skirt from the left edge, which a band a few
+// vectors narrower gives.
+template <typename Cfg, int W, typename TC>
+bool valu2d_bands(const PassArgs &p, Valu2DJob<TC> *g)
+{
+    constexpr int BXmax = Cfg::NCW - 2 * Cfg::E;
+    static_assert(BXmax > 0, "band narrower than its skirt");
     g->src = p.src;
     g->dst = p.dst;
     g->n0 = (int)p.dims[0];
@@ -612,58 +569,211 @@ bool valu2d_geometry(const PassArgs &p, Valu2DJob<TC> *g, hipError_t *err)
     g->ox1 = p.region_hi[1];
     g->periodic = p.boundary == STENCIL_PERIODIC;
     g->h = (TC)p.halo;
-    g->BX = Cfg::NCW - 2 * Cfg::E;
-    if (g->BX <= 0) {
-        *err = hipErrorInvalidValue;
-        return false;
-    }
-    const int W_out = g->ox1 - g->ox0, H_out = g->oy1 - g->oy0;
-    if (W_out <= 0 || H_out <= 0) return false;
-    g->nbands = (W_out + g->BX - 1) / g->BX;
-    // rows per wave: the wave count is a whole number of waves of the resident
-    // slots (waves per CU x CUs), as few rounds as keep segments long enough to
-    // amortise the 2rT + T pipeline rows
-    int BY = p.tile_rows;
-    if (BY <= 0) {
-        const int slots = (p.num_cu > 0 ? p.num_cu : 256) * (p.slots_per_cu > 0 ? p.slots_per_cu : 8);
-        const int minBY = 16 * (2 * R * T + T) > 64 ? 16 * (2 * R * T + T) : 64;
-        const int groups = (g->nbands + kValu2DWaves - 1) / kValu2DWaves;
-        int segs = 1;
-        for (int rounds = 1; rounds <= 64; ++rounds) {
-            segs = (rounds * slots) / (groups * kValu2DWaves);
-            if (segs < 1) segs = 1;
-            if ((H_out + segs - 1) / segs <= 4 * minBY) break;
+    g->anchor = -1;
+    g->BX = BXmax;
+    if (W > 1 && (g->n1 % W != 0 || g->ox0 % W != 0)) {
+        if (g->ox0 != 0 || g->ox1 != g->n1 || g->n1 < Cfg::NCW) return false;
+        for (;; g->BX -= W) {
+            if (g->BX < BXmax / 2) return false;
+            const int nb = (g->n1 + g->BX - 1) / g->BX;
+            g->anchor = g->n1 - (nb - 1) * g->BX;
+            if (nb >= 2 && g->anchor >= Cfg::E) break;
         }
-        BY = (H_out + segs - 1) / segs;
-        if (BY < 16) BY = 16;
     }
-    g->BY = BY;
-    g->nsegs = (H_out + BY - 1) / BY;
-    g->nwg = ((g->nbands + kValu2DWaves - 1) / kValu2DWaves) * g->nsegs;
+    g->nbands = (g->ox1 - g->ox0 + g->BX - 1) / g->BX;
     return true;
+}
+
+// Row segments of BY rows.
+template <typename TC>
+void valu2d_rows(Valu2DJob<TC> *g, int BY)
+{
+    const int H = g->oy1 - g->oy0;
+    g->BY = BY;
+    g->nsegs = (H + BY - 1) / BY;
+    g->nwg = (int)(((int64_t)g->nbands * g->nsegs + kValu2DWaves - 1) / kValu2DWaves);
+}
+
+// Resident workgroups per CU of a kernel instance.
+template <typename K>
+int valu2d_occupancy(K kernel)
+{
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 64 * kValu2DWaves, 0) != hipSuccess || occ < 1)
+        occ = 1;
+    return occ;
+}
+
+// Estimate of a launch of nwg workgroups over segments of BY rows, in cycles:
+// the larger of the rows' issue time and the bytes' time.
+//   issue: a wave takes BY + 2RT + T row iterations.  One costs about 1500
+//     cycles of latency shared by the waves of a SIMD (permutes, the stages'
+//     chains; 100 more per streamed weight column) and the instructions of
+//     each of them.  A workgroup puts one wave on every SIMD of its CU, so the
+//     busiest CU's workgroups, not the average, count (8192^2 float32
+//     Star-2D3R T = 4: 504 workgroups = 2 per CU 171 us, 576 279).
+//   bytes: one read and one write per point, the read grown by the skirt and
+//     the halo rows, at about 1800 bytes a cycle from HBM or 3500 from the
+//     last-level cache (256 MB).
+// Fitted to 216 variants and sizes (72 variants, 300^2..8192^2, 45 choices
+// each): the choice is 2.4 % behind the best measured on average.
+template <typename Cfg, typename TS, typename TC, int SHAPE, int R, int T, int W>
+struct Valu2DCost {
+    static double issue(int64_t nwg, int BY, int occ, int cus)
+    {
+        const double row =
+            T * (W * ((sizeof(TC) == 8 ? 4.5 : 2.5) * Cfg::K + 32) + 12.0 * 2 * R * (sizeof(TC) / 4)) + 20;
+        const double latency = 1500 + (Cfg::WPTR ? 100.0 * Cfg::Q * (T >= 3 ? 1 : T) : 0.0);
+        auto resident = [&](int64_t k) { return latency + row * (k > 1 ? k - 0.4 : k); };
+        const int64_t per_cu = (nwg + cus - 1) / cus, full = per_cu / occ, rest = per_cu % occ;
+        return (BY + 2 * R * T + T) * (full * resident(occ) + (rest ? resident(rest) : 0.0));
+    }
+    static double memory(double points, int BY, int BX)
+    {
+        const double grow = (1.0 + 2.0 * R * T / BY) * Cfg::NCW / BX;
+        return points * sizeof(TS) * (1.0 + grow) / (2 * points * sizeof(TS) > 256e6 ? 1800.0 : 3500.0);
+    }
+};
+
+struct Valu2DPick {
+    int W = 0, BY = 0;
+    double cost = -1.0;
+    // short segments on a grid past the last-level cache
+    bool streams = false;
+};
+
+inline double valu2d_points(const PassArgs &p)
+{
+    return (double)std::max(p.region_hi[0] - p.region_lo[0], 0) * std::max(p.region_hi[1] - p.region_lo[1], 0);
+}
+
+// Try W columns per lane for a launch over n passes: segment lengths that put
+// 1..32 workgroups on every CU, none under 3 rows.
+template <typename TS, typename TC, int SHAPE, int R, int T, int W>
+void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
+{
+    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, W>;
+    using Cost = Valu2DCost<Cfg, TS, TC, SHAPE, R, T, W>;
+    int64_t bands = 0;
+    int hmax = 1, bx = 1;
+    double points = 0, area = 0;  // area: bands x rows
+    Valu2DJob<TC> g;
+    for (int i = 0; i < n; ++i) {
+        const int H = ps[i].region_hi[0] - ps[i].region_lo[0];
+        if (H <= 0 || valu2d_points(ps[i]) <= 0) continue;
+        if (!valu2d_bands<Cfg, W>(ps[i], &g)) return;
+        bands += g.nbands;
+        area += (double)g.nbands * H;
+        points += valu2d_points(ps[i]);
+        hmax = std::max(hmax, H);
+        bx = g.BX;
+    }
+    auto workgroups = [&](int BY) {
+        int64_t items = 0;
+        for (int i = 0; i < n; ++i) {
+            const int H = ps[i].region_hi[0] - ps[i].region_lo[0];
+            if (H <= 0 || valu2d_points(ps[i]) <= 0) continue;
+            if (n > 1) valu2d_bands<Cfg, W>(ps[i], &g);
+            items += (int64_t)g.nbands * ((H + BY - 1) / BY);
+        }
+        return (items + kValu2DWaves - 1) / kValu2DWaves;
+    };
+    auto consider = [&](int BY, bool streams, double cost) {
+        if (best->cost >= 0 && (best->streams > streams || (best->streams == streams && cost >= best->cost))) return;
+        *best = {W, BY, cost, streams};
+    };
+    if (n == 1 && ps[0].tile_rows > 0) {  // the caller's segment length
+        const int BY = ps[0].tile_rows;
+        consider(BY, false, std::max(Cost::issue(workgroups(BY), std::min(BY, hmax), occ, cus),
+                                     Cost::memory(points, BY, bx)));
+        return;
+    }
+    static const int kPerCu[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32};
+    int last = 0;
+    for (int k : kPerCu) {
+        // n passes: a common length of about area / items rows
+        const int64_t items = (int64_t)k * kValu2DWaves * cus;
+        const int64_t segs = items / std::max<int64_t>(bands, 1);
+        if (n == 1 && segs < 1) continue;
+        int BY = n == 1 ? (int)((hmax + segs - 1) / segs) : (int)(area / items) + 1;
+        if (BY < 3) BY = 3;
+        if (BY == last) break;
+        last = BY;
+        const double issue = Cost::issue(workgroups(BY), std::min(BY, hmax), occ, cus);
+        // Past the last-level cache a memory-bound pass gains from short
+        // segments, whose workgroups walk the grid together (8192^2 float64
+        // Star-2D1R T = 1: 17 rows 212 us, 137 232; float32 107, 119): the
+        // shortest ones where their issue time is within 1.4 of the bytes'.
+        const bool streams = k == 32 && W == (sizeof(TS) == 8 ? 2 : 4) && 2 * points * sizeof(TS) > 256e6 &&
+                             issue < 1.4 * 2 * points * sizeof(TS) / 1800.0;
+        consider(BY, streams, std::max(issue, Cost::memory(points, BY, bx)));
+    }
+    // fewer bands of work than one workgroup per CU: whole columns
+    if (best->cost < 0) consider(hmax, false, Cost::issue(workgroups(hmax), hmax, occ, cus));
+}
+
+// Geometry of one pass for W columns per lane and segments of BY rows.
+template <typename TS, typename TC, int SHAPE, int R, int T, int W>
+void valu2d_geometry(const PassArgs &p, int BY, Valu2DJob<TC> *g)
+{
+    (void)valu2d_bands<Valu2DCfg<TS, TC, SHAPE, R, T, W>, W>(p, g);
+    valu2d_rows(g, BY);
+}
+
+template <typename TS, typename TC, int SHAPE, int R, int T, int W>
+hipError_t launch_valu2d_width(const PassArgs &p, int BY, hipStream_t stream)
+{
+    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, W>;
+    Valu2DArgs<TC, Cfg::K> a;
+    valu2d_geometry<TS, TC, SHAPE, R, T, W>(p, BY, &a.g);
+    for (int k = 0; k < Cfg::K; ++k) a.w[weight_slot<Cfg, R>(k)] = (TC)p.w[k];
+    hipLaunchKernelGGL((valu2d_kernel<TS, TC, SHAPE, R, T, W>), dim3(a.g.nwg), dim3(64 * kValu2DWaves), 0, stream, a);
+    return hipGetLastError();
 }
 
 template <typename TS, typename TC, int SHAPE, int R, int T>
 hipError_t launch_valu2d(const PassArgs &p, hipStream_t stream)
 {
-    using S = Valu2DShape<TS, R, T>;
-    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, S::W>;
-    Valu2DArgs<TC, Cfg::K> a;
-    hipError_t err;
-    static const int occ = [] {  // resident waves per CU of this instance
-        int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, valu2d_kernel<TS, TC, SHAPE, R, T, S::W>,
-                                                         64 * kValu2DWaves, 0) != hipSuccess || o < 1)
-            o = 2;
-        return o * kValu2DWaves;
-    }();
-    PassArgs q = p;
-    q.slots_per_cu = occ;
-    if (!valu2d_geometry<TS, TC, SHAPE, R, T>(q, &a.g, &err)) return err;
-    for (int k = 0; k < Cfg::K; ++k) a.w[weight_slot<Cfg, R>(k)] = (TC)p.w[k];
-    const int grid = a.g.nwg;
-    hipLaunchKernelGGL((valu2d_kernel<TS, TC, SHAPE, R, T, S::W>), dim3(grid), dim3(64 * kValu2DWaves), 0,
-                       stream, a);
+    if (valu2d_points(p) <= 0) return hipSuccess;
+    static const int occ1 = valu2d_occupancy(valu2d_kernel<TS, TC, SHAPE, R, T, 1>);
+    static const int occ2 = valu2d_occupancy(valu2d_kernel<TS, TC, SHAPE, R, T, 2>);
+    const int cus = p.num_cu > 0 ? p.num_cu : 256;
+    Valu2DPick pick;
+    valu2d_try<TS, TC, SHAPE, R, T, 1>(&p, 1, occ1, cus, &pick);
+    valu2d_try<TS, TC, SHAPE, R, T, 2>(&p, 1, occ2, cus, &pick);
+    if constexpr (valu2d_widest<TC, T>() == 4) {
+        static const int occ4 = valu2d_occupancy(valu2d_kernel<TS, TC, SHAPE, R, T, 4>);
+        valu2d_try<TS, TC, SHAPE, R, T, 4>(&p, 1, occ4, cus, &pick);
+        if (pick.W == 4) return launch_valu2d_width<TS, TC, SHAPE, R, T, 4>(p, pick.BY, stream);
+    }
+    return pick.W == 2 ? launch_valu2d_width<TS, TC, SHAPE, R, T, 2>(p, pick.BY, stream)
+                       : launch_valu2d_width<TS, TC, SHAPE, R, T, 1>(p, pick.BY, stream);
+}
+
+template <typename TS, typename TC, int SHAPE, int R, int T, int W>
+hipError_t launch_valu2d_batch_width(const PassArgs *ps, int n, int BY, int slots, BatchStaging *stage,
+                                     hipStream_t stream)
+{
+    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, W>;
+    using Job = Valu2DBatchJob<TC, Cfg::K>;
+    std::vector<Job> jobs;
+    std::vector<int> start(1, 0);
+    jobs.reserve(n);
+    for (int i = 0; i < n; ++i) {
+        if (valu2d_points(ps[i]) <= 0) continue;
+        Job j;
+        valu2d_geometry<TS, TC, SHAPE, R, T, W>(ps[i], ps[i].tile_rows > 0 ? ps[i].tile_rows : BY, &j.g);
+        for (int k = 0; k < Cfg::K; ++k) j.w[weight_slot<Cfg, R>(k)] = (TC)ps[i].w[k];
+        jobs.push_back(j);
+        start.push_back(start.back() + j.g.nwg);
+    }
+    void *djobs = nullptr, *dstart = nullptr;
+    hipError_t e = stage_job_table(stage, jobs.data(), jobs.size() * sizeof(Job), start, &djobs, &dstart, stream);
+    if (e != hipSuccess) return e;
+    const int total = start.back();
+    hipLaunchKernelGGL((valu2d_batch_kernel<TS, TC, SHAPE, R, T, W>), dim3(total < slots ? total : slots),
+                       dim3(64 * kValu2DWaves), 0, stream, static_cast<const Job *>(djobs),
+                       static_cast<const int *>(dstart), (int)jobs.size());
     return hipGetLastError();
 }
 
@@ -671,39 +781,24 @@ hipError_t launch_valu2d(const PassArgs &p, hipStream_t stream)
 template <typename TS, typename TC, int SHAPE, int R, int T>
 hipError_t launch_valu2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    using S = Valu2DShape<TS, R, T>;
-    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, S::W>;
-    using Job = Valu2DBatchJob<TC, Cfg::K>;
-    std::vector<Job> jobs;
-    std::vector<int> start(1, 0);
-    jobs.reserve(n);
-    for (int i = 0; i < n; ++i) {
-        Job j;
-        hipError_t err;
-        if (!valu2d_geometry<TS, TC, SHAPE, R, T>(ps[i], &j.g, &err)) {
-            if (err != hipSuccess) return err;
-            continue;
-        }
-        for (int k = 0; k < Cfg::K; ++k) j.w[weight_slot<Cfg, R>(k)] = (TC)ps[i].w[k];
-        jobs.push_back(j);
-        start.push_back(start.back() + j.g.nwg);
+    bool any = false;
+    for (int i = 0; i < n; ++i) any = any || valu2d_points(ps[i]) > 0;
+    if (!any) return hipSuccess;
+    static const int occ1 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 1>);
+    static const int occ2 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 2>);
+    const int cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
+    Valu2DPick pick;
+    valu2d_try<TS, TC, SHAPE, R, T, 1>(ps, n, occ1, cus, &pick);
+    valu2d_try<TS, TC, SHAPE, R, T, 2>(ps, n, occ2, cus, &pick);
+    if constexpr (valu2d_widest<TC, T>() == 4) {
+        static const int occ4 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 4>);
+        valu2d_try<TS, TC, SHAPE, R, T, 4>(ps, n, occ4, cus, &pick);
+        if (pick.W == 4)
+            return launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 4>(ps, n, pick.BY, occ4 * cus, stage, stream);
     }
-    if (jobs.empty()) return hipSuccess;
-    const int nj = (int)jobs.size();
-    void *djobs = nullptr, *dstart = nullptr;
-    hipError_t e = stage_job_table(stage, jobs.data(), jobs.size() * sizeof(Job), start, &djobs, &dstart, stream);
-    if (e != hipSuccess) return e;
-    const int total_wg = start.back();
-    int occ = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &occ, valu2d_batch_kernel<TS, TC, SHAPE, R, T, S::W>, 64 * kValu2DWaves, 0);
-    if (e != hipSuccess || occ < 1) occ = 1;
-    const int slots = occ * (ps[0].num_cu > 0 ? ps[0].num_cu : 256);
-    const int grid = total_wg < slots ? total_wg : slots;
-    hipLaunchKernelGGL((valu2d_batch_kernel<TS, TC, SHAPE, R, T, S::W>), dim3(grid),
-                       dim3(64 * kValu2DWaves), 0, stream, static_cast<const Job *>(djobs),
-                       static_cast<const int *>(dstart), nj);
-    return hipGetLastError();
+    return pick.W == 2
+               ? launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 2>(ps, n, pick.BY, occ2 * cus, stage, stream)
+               : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps, n, pick.BY, occ1 * cus, stage, stream);
 }
 
 #define V2(TS, TC, DT, SH, R, T) \

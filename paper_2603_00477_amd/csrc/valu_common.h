@@ -76,6 +76,10 @@ struct RawVec {
             __builtin_memcpy(e, &v, 4);
         }
     }
+    // the same at any element address (gfx950 loads and stores vectors at
+    // element alignment; the compiler emits the 16-byte instructions)
+    __device__ __forceinline__ void load_any(const TS *p) { __builtin_memcpy(e, p, sizeof(TS) * W); }
+    __device__ __forceinline__ void store_any(TS *p) const { __builtin_memcpy(p, e, sizeof(TS) * W); }
     __device__ __forceinline__ void store(TS *p) const
     {
         if constexpr (sizeof(TS) * W == 32) {
