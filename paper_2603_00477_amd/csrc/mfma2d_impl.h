@@ -584,7 +584,14 @@ __device__ __forceinline__ void mfma2d_tile(const Mfma2DArgs &a, const int tile)
 // transposition); for every composite row a and k-block the wave issues one
 // MFMA per stacked tile with the weight band as operand A and 8 consecutive
 // columns of one data row per lane as operand B; the transposed 16 x 16
-// results give each lane 4 consecutive output columns of one row.
+// results give each lane 4 consecutive output columns of one row.  The stacked
+// tiles interleave their rows (tile v holds rows V ln + v), so that one
+// operand-B read serves up to V of them.
+//
+// What bounds it: HBM latency, then the matrix units (bf16 Box-2D2R 16384^2:
+// T = 1 / 2 / 4 253 / 271 / 290 us a pass of 1.07 GB, 4.2 TB/s at T = 1; 17
+// MFMAs per 16 x 16 tile take about 126 us at T = 4).  Before the interleaved
+// rows and sixteen-wave tiles: 271 / 305 / 365 us.
 template <int DT, int SHAPE, int r, int T, int V, int NW>
 struct RowsCfg {
     using MT = MfmaTypes<DT>;
@@ -600,14 +607,20 @@ struct RowsCfg {
     static constexpr int KMAX = 16 * (NW - 1) + 32 * NKB0;                  // frame columns read
     static constexpr int LCD = TC + 2 * R + DL;                             // frame columns holding data
     static constexpr int LCF = ((KMAX > LCD ? KMAX : LCD) + 7) / 8 * 8;     // staged columns
-    // row pitch in 16-byte units: 2 mod 4 for eight-wave tiles, which makes
-    // the operand-B reads conflict-free (measured on 16384^2: bf16 Box-2D2R
-    // T = 4 2766 -> 2968, Star-2D2R T = 4 2839 -> 3075 GSt/s against an odd
-    // pitch); odd for four-wave tiles (1-2 % faster there than the others)
-    static constexpr int PIT = NW == 8 ? LCF + 8 * ((2 - (LCF / 8) % 4 + 4) % 4)
-                                       : ((LCF / 8) % 2 ? LCF : LCF + 8);
+    // row pitch in 16-byte units: 2 mod 4, which makes the operand-B reads
+    // conflict-free (measured on 16384^2: bf16 Box-2D2R T = 4 2766 -> 2968,
+    // Star-2D2R T = 4 2839 -> 3075 GSt/s against an odd pitch); lanes read rows
+    // V apart, so V is odd to keep the stride 2 mod 4 too
+    static_assert(V % 2 == 1, "lane stride must stay 2 mod 4 units");
+    static constexpr int PIT = LCF + 8 * ((2 - (LCF / 8) % 4 + 4) % 4);
     static constexpr int NFRAG = rows_total_frags(SHAPE, r, T);
     static constexpr bool ALDS = NFRAG <= 24;
+    // whether composite row ar has weights in k-block kb
+    static constexpr bool uses(int ar, int kb)
+    {
+        return ar >= -R && ar <= R && rows_nblk(SHAPE, r, T, ar) > 0 && kb >= rows_kk_lo(SHAPE, r, T, ar) &&
+               kb <= rows_kk_hi(SHAPE, r, T, ar);
+    }
     static constexpr int NCH = LCF / 8;                                     // 16-byte chunks per frame row
     static constexpr int NE = (LRD * NCH + NT - 1) / NT;                    // chunks per thread
     // a 16-byte chunk as a plain vector type (a struct with unions would be
@@ -617,12 +630,12 @@ struct RowsCfg {
     // frame origin in the grid (column a multiple of 8)
     __device__ __forceinline__ static int fr0(const Mfma2DArgs &a, int tile) { return (tile / a.ntc) * TR - R; }
     __device__ __forceinline__ static int fc0(const Mfma2DArgs &a, int tile) { return (tile % a.ntc) * TC - R - DL; }
-    // interior tile: the frame lies inside the grid, rows of whole 16-byte units
+    // interior tile: the frame lies inside the grid (loads need no alignment
+    // beyond the element)
     __device__ __forceinline__ static bool fast(const Mfma2DArgs &a, int tile)
     {
         const int f0 = fr0(a, tile), g0 = fc0(a, tile);
-        return f0 >= 0 && f0 + LRD <= a.n0 && g0 >= 0 && g0 + LCF <= a.n1 && (a.n1 % 8) == 0 &&
-               (reinterpret_cast<uintptr_t>(a.src) % 16) == 0;
+        return f0 >= 0 && f0 + LRD <= a.n0 && g0 >= 0 && g0 + LCF <= a.n1;
     }
     // issue the frame loads of an interior tile, chunks i = 0..NE-1 of this
     // thread; clamped indices: every lane loads (in bounds), so the loads
@@ -636,7 +649,9 @@ struct RowsCfg {
             const int e = tid + i * NT;
             const int ec = e < LRD * NCH ? e : LRD * NCH - 1;
             const int rowc = ec / NCH, chc = ec - rowc * NCH;
-            v[i] = *reinterpret_cast<const Chunk *>(src + (int64_t)(f0 + rowc) * n1 + g0 + 8 * chc);
+            RawVec<TS, 8> c;
+            c.load_any(src + (int64_t)(f0 + rowc) * n1 + g0 + 8 * chc);
+            __builtin_memcpy(&v[i], c.e, sizeof(Chunk));
         }
     }
     __device__ __forceinline__ static void write(const Chunk (&v)[NE], OP *lb, int tid)
@@ -648,27 +663,57 @@ struct RowsCfg {
             if (e < LRD * NCH) *reinterpret_cast<Chunk *>(&lb[row * PIT + 8 * ch]) = v[i];
         }
     }
-    // edge tiles: element by element with the boundary rule; columns past
-    // the data (read only against zero weights) get zeros
-    __device__ __forceinline__ static void stage_slow(const Mfma2DArgs &a, int tile, OP *lb, int tid)
+    // edge tiles: a chunk inside
+    // the grid (after the periodic wrap of its first column) is one load at
+    // element alignment, one outside a Dirichlet grid is h, and only a chunk
+    // that straddles an edge goes element by element.  All chunks load
+    // unconditionally (a valid dummy where they must not), so the loads stay in
+    // flight together.  Columns past the data (read only against zero
+    // weights) get zeros.
+    __device__ __forceinline__ static void stage_edge(const Mfma2DArgs &a, int tile, OP *lb, int tid)
     {
         const TS *src = static_cast<const TS *>(a.src);
         const int f0 = fr0(a, tile), g0 = fc0(a, tile), n0 = a.n0, n1 = a.n1;
         const bool periodic = a.periodic != 0;
-        for (int e = tid; e < LRD * LCF; e += NT) {
-            const int row = e / LCF, col = e - row * LCF;
-            int gr = f0 + row, gc = g0 + col;
-            OP v = OP(0);
-            if (col < LCD) {
-                const bool in = gr >= 0 && gr < n0 && gc >= 0 && gc < n1;
-                v = to_op<OP>(a.h);
-                if (in || periodic) {
-                    gr = wrap(gr, n0);
-                    gc = wrap(gc, n1);
-                    v = to_op<OP>(load_val(src[(int64_t)gr * n1 + gc]));
-                }
+        const OP h = to_op<OP>(a.h);
+        constexpr int CB = NE < 8 ? NE : 8;
+#pragma unroll
+        for (int e0 = 0; e0 < NE; e0 += CB) {
+            RawVec<TS, 8> v[CB];
+#pragma unroll
+            for (int i = 0; i < CB; ++i) {
+                const int e = min(tid + (e0 + i) * NT, LRD * NCH - 1);
+                const int row = e / NCH, gr = f0 + row, gc = g0 + 8 * (e - row * NCH);
+                const int sr = periodic ? wrap(gr, n0) : min(max(gr, 0), n0 - 1);
+                const int sc = periodic ? wrap(gc, n1) : min(max(gc, 0), n1 - 1);
+                if (n1 >= 8) v[i].load_any(src + (int64_t)sr * n1 + min(sc, n1 - 8));
             }
-            lb[row * PIT + col] = v;
+#pragma unroll
+            for (int i = 0; i < CB; ++i) {
+                const int e = tid + (e0 + i) * NT;
+                if (e0 + i >= NE || e >= LRD * NCH) break;
+                const int row = e / NCH, gr = f0 + row, c = 8 * (e - row * NCH), gc = g0 + c;
+                const bool rin = gr >= 0 && gr < n0;
+                const int sc = periodic ? wrap(gc, n1) : gc;
+                typedef OP OP8 __attribute__((ext_vector_type(8)));
+                OP8 o;
+                if (c >= LCD) {
+                    o = OP8(OP(0));
+                } else if (sc >= 0 && sc + 8 <= n1 && (rin || periodic)) {
+                    __builtin_memcpy(&o, v[i].e, 16);
+                } else if (!periodic && (!rin || gc + 8 <= 0 || gc >= n1)) {
+                    o = OP8(h);
+                } else {
+                    const TS *rowp = src + (int64_t)(periodic ? wrap(gr, n0) : gr) * n1;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int cj = gc + j;
+                        o[j] = periodic ? to_op<OP>(load_val(rowp[wrap(cj, n1)]))
+                                        : (cj >= 0 && cj < n1 ? to_op<OP>(load_val(rowp[cj])) : h);
+                    }
+                }
+                *reinterpret_cast<OP8 *>(&lb[row * PIT + c]) = o;
+            }
         }
     }
     // MFMAs over the staged frame and the store of the tile
@@ -681,38 +726,49 @@ struct RowsCfg {
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = ACC{};
         const int colw = 16 * wave + 8 * lg;
+        // tile v holds output rows V ln + v, so operand B of (tile v, composite
+        // row ar) is data row V ln + (v + ar): one read serves every pair with
+        // the same sum, 2R + V reads per k-block in place of V (2R + 1)
+        FR A[V][NKB0];
 #pragma unroll
-        for (int ar = -R; ar <= R; ++ar) {
-            if (band_amax(SHAPE, r, T, 0, ar) < 0) continue;
-            const int klo = rows_kk_lo(SHAPE, r, T, ar), nb = rows_nblk(SHAPE, r, T, ar);
-            const int off = rows_frag_offset(SHAPE, r, T, ar);
+        for (int s = 0; s <= 2 * R + V - 1; ++s) {
+            if (s <= 2 * R) {
+                const int ar = s - R;
 #pragma unroll
-            for (int ib = 0; ib < nb; ++ib) {
-                const FR A = ALDS ? lA[(off + ib) * 64 + lane] : afr[(off + ib) * 64 + lane];
-                const int col = colw + 32 * (klo + ib);
+                for (int kb = 0; kb < NKB0; ++kb)
+                    if (uses(ar, kb)) {
+                        const int f = (rows_frag_offset(SHAPE, r, T, ar) + kb - rows_kk_lo(SHAPE, r, T, ar)) * 64 + lane;
+                        A[s % V][kb] = ALDS ? lA[f] : afr[f];
+                    }
+            }
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    const FR B = *reinterpret_cast<const FR *>(&lb[(16 * v + ln + ar + R) * PIT + col]);
-                    acc[v] = mfma16(A, B, acc[v]);
-                }
+            for (int kb = 0; kb < NKB0; ++kb) {
+                bool any = false;
+#pragma unroll
+                for (int v = 0; v < V; ++v) any = any || uses(s - v - R, kb);
+                if (!any) continue;
+                const FR B = *reinterpret_cast<const FR *>(&lb[(V * ln + s) * PIT + colw + 32 * kb]);
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (uses(s - v - R, kb)) acc[v] = mfma16(A[(s - v + V) % V][kb], B, acc[v]);
             }
         }
-        // lane (lg, ln) holds row r0 + 16 v + ln, columns 4 lg .. 4 lg + 3
+        // lane (lg, ln) holds row r0 + V ln + v, columns 4 lg .. 4 lg + 3
         TS *dst = static_cast<TS *>(a.dst);
         const int n0 = a.n0, n1 = a.n1;
         const int r0 = (tile / a.ntc) * TR, c0 = (tile % a.ntc) * TC;
         const int gc = c0 + 16 * wave + 4 * lg;
-        const bool vec = gc + 4 <= n1 && (n1 % 4) == 0 && (reinterpret_cast<uintptr_t>(dst) % 8) == 0;
+        const bool vec = gc + 4 <= n1;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const int gr = r0 + 16 * v + ln;
+            const int gr = r0 + V * ln + v;
             if (gr >= n0 || gc >= n1) continue;
             TS *p = dst + (int64_t)gr * n1 + gc;
             if (vec) {
                 RawVec<TS, 4> ov;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ov.e[e] = to_storage<TS>(acc[v][e]);
-                ov.store(p);
+                ov.store_any(p);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -752,7 +808,7 @@ __device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int 
         C::issue(a, tile, v, tid);
         C::write(v, lb, tid);
     } else {
-        C::stage_slow(a, tile, lb, tid);
+        C::stage_edge(a, tile, lb, tid);
     }
     if constexpr (C::ALDS) {
 #pragma unroll
@@ -777,7 +833,7 @@ constexpr bool use_rows()
 }
 
 template <int DT, int SHAPE, int r, int T, int V, int NW, bool SP>
-__global__ __launch_bounds__(64 * NW) void mfma2d_kernel(Mfma2DArgs a)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW >= 16 ? 8 : 1))) void mfma2d_kernel(Mfma2DArgs a)
 {
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= a.ntiles) return;
@@ -792,7 +848,7 @@ __global__ __launch_bounds__(64 * NW) void mfma2d_kernel(Mfma2DArgs a)
 // (tile_start[njobs] = total).  A barrier between items keeps the next
 // item's staging from overwriting LDS blocks still being read.
 template <int DT, int SHAPE, int r, int T, int V, int NW, bool SP>
-__global__ __launch_bounds__(64 * NW) void mfma2d_batch_kernel(const Mfma2DArgs *__restrict__ jobs,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW >= 16 ? 8 : 1))) void mfma2d_batch_kernel(const Mfma2DArgs *__restrict__ jobs,
                                                              const int *__restrict__ tile_start, int njobs)
 {
     const int total = tile_start[njobs];
@@ -808,30 +864,37 @@ __global__ __launch_bounds__(64 * NW) void mfma2d_batch_kernel(const Mfma2DArgs 
     }
 }
 
-// 16-bit operands: eight waves side by side (64 x 128 workgroup tiles,
-// a smaller halo share).  With the conflict-free row pitch of these tiles
-// they measured faster at every depth on 16384^2 (bf16 Box-2D2R T = 1 / 2 /
-// 4: 856 -> 949, 1644 -> 1814, 2766 -> 2978 GSt/s; Box-2D1R T = 1 848 ->
-// 987); with an odd pitch, small composite radii had been up to 12 % slower
-// with eight.  The compensated mode's column-layout tiles gain too (bf16x3
-// Box-2D2R T = 2 / 4: 886 -> 974, 1211 -> 1272 GSt/s).  Dense (not 2:4
-// sparse) 16-bit
-// passes with r <= 2 and composite radius 2-4 stack six tiles per wave (96 x
-// 128: fewer halo rows per output row; +0.5-3 % measured, e.g. Star-2D2R
-// T = 2 1806 -> 1858, Box-2D1R T = 4 3610 -> 3696 GSt/s); Box-2D3R T = 1
-// was 8 % slower with six.
-template <int DT, int r, int T, bool SP = false>
+// Tile shapes.  Column layout: 16-bit operands take eight waves side by side
+// (compensated bf16x3 Box-2D2R T = 2 / 4 886 -> 974, 1211 -> 1272 GSt/s against
+// four), float64/float32 four.  Row layout: three stacked tiles of eight waves
+// (48 x 128 points), or, where a pass moves more than the last-level cache
+// holds (256 MB), five tiles of sixteen waves (80 x 256), held to 64 registers
+// so that two workgroups keep 32 waves on a CU: HBM latency is the bound there.
+// bf16 Box-2D2R, us per pass, 3 x 8 | 5 x 8 | 5 x 16:
+//   T = 4: 1024^2 5.1 | 6.1 | 8.4, 4096^2 21.5 | 22.6 | 23.7,
+//          8192^2 74 | 73 | 75, 16384^2 352 | 326 | 292
+//   T = 2: 4096^2 19.3 | 21.2 | 21.9, 16384^2 298 | 282 | 275
+template <int DT>
 struct Mfma2DShape {
-    static constexpr int V =
-        (MfmaTypes<DT>::KDIM == 32 && !MfmaTypes<DT>::X3 && !SP && r <= 2 && r * T >= 2 && r * T <= 4) ? 6 : 4;
+    static constexpr int V = 4;
     static constexpr int NW = MfmaTypes<DT>::KDIM == 32 ? 8 : 4;
 };
-
-template <int DT, int SHAPE, int r, int T, bool SP = false>
-bool mfma2d_args(const PassArgs &p, Mfma2DArgs *out)
+struct RowsSmall {
+    static constexpr int V = 3, NW = 8;
+};
+struct RowsLarge {
+    static constexpr int V = 5, NW = 16;
+};
+inline bool rows_large(const PassArgs *ps, int n)
 {
-    constexpr int V = Mfma2DShape<DT, r, T, SP>::V, NW = Mfma2DShape<DT, r, T, SP>::NW;
-    using Cfg = Mfma2DCfg<DT, SHAPE, r, T, V, NW>;
+    double bytes = 0;
+    for (int i = 0; i < n; ++i) bytes += 4.0 * ps[i].dims[0] * ps[i].dims[1];  // 2 bytes in, 2 out
+    return bytes > 256e6;
+}
+
+template <int DT, typename S>
+bool mfma2d_args(const PassArgs &p, int T, Mfma2DArgs *out)
+{
     if (p.steps != T || !p.afrag) return false;
     if (MfmaTypes<DT>::X3 && !p.afrag_lo) return false;
     Mfma2DArgs &a = *out;
@@ -843,35 +906,42 @@ bool mfma2d_args(const PassArgs &p, Mfma2DArgs *out)
     a.n1 = (int)p.dims[1];
     a.periodic = p.boundary == STENCIL_PERIODIC;
     a.h = p.halo;
-    a.ntr = (a.n0 + Cfg::TR - 1) / Cfg::TR;
-    a.ntc = (a.n1 + Cfg::TCOL - 1) / Cfg::TCOL;
+    a.ntr = (a.n0 + 16 * S::V - 1) / (16 * S::V);
+    a.ntc = (a.n1 + 16 * S::NW - 1) / (16 * S::NW);
     a.ntiles = a.ntr * a.ntc;
     return true;
+}
+
+template <int DT, int SHAPE, int r, int T, typename S, bool SP>
+hipError_t launch_mfma2d_shape(const PassArgs &p, hipStream_t stream)
+{
+    Mfma2DArgs a;
+    if (!mfma2d_args<DT, S>(p, T, &a)) return hipErrorInvalidValue;
+    if (a.ntiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL((mfma2d_kernel<DT, SHAPE, r, T, S::V, S::NW, SP>), dim3(a.ntiles), dim3(64 * S::NW), 0, stream,
+                       a);
+    return hipGetLastError();
 }
 
 template <int DT, int SHAPE, int r, int T, bool SP = false>
 hipError_t launch_mfma2d(const PassArgs &p, hipStream_t stream)
 {
-    constexpr int V = Mfma2DShape<DT, r, T, SP>::V, NW = Mfma2DShape<DT, r, T, SP>::NW;
-    Mfma2DArgs a;
-    if (!mfma2d_args<DT, SHAPE, r, T, SP>(p, &a)) return hipErrorInvalidValue;
-    if (a.ntiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL((mfma2d_kernel<DT, SHAPE, r, T, V, NW, SP>), dim3(a.ntiles), dim3(64 * NW), 0, stream,
-                       a);
-    return hipGetLastError();
+    if constexpr (use_rows<DT, SHAPE, r, T, SP>())
+        return rows_large(&p, 1) ? launch_mfma2d_shape<DT, SHAPE, r, T, RowsLarge, SP>(p, stream)
+                                 : launch_mfma2d_shape<DT, SHAPE, r, T, RowsSmall, SP>(p, stream);
+    else
+        return launch_mfma2d_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(p, stream);
 }
 
-// n passes (one per job) of this variant in one persistent launch.
-template <int DT, int SHAPE, int r, int T, bool SP = false>
-hipError_t launch_mfma2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+template <int DT, int SHAPE, int r, int T, typename S, bool SP>
+hipError_t launch_mfma2d_batch_shape(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    constexpr int V = Mfma2DShape<DT, r, T, SP>::V, NW = Mfma2DShape<DT, r, T, SP>::NW;
     std::vector<Mfma2DArgs> jobs;
     std::vector<int> start(1, 0);
     jobs.reserve(n);
     for (int i = 0; i < n; ++i) {
         Mfma2DArgs a;
-        if (!mfma2d_args<DT, SHAPE, r, T, SP>(ps[i], &a)) return hipErrorInvalidValue;
+        if (!mfma2d_args<DT, S>(ps[i], T, &a)) return hipErrorInvalidValue;
         if (a.ntiles <= 0) continue;
         if ((int64_t)start.back() + a.ntiles > (1LL << 30)) return hipErrorInvalidValue;
         jobs.push_back(a);
@@ -882,16 +952,26 @@ hipError_t launch_mfma2d_batch(const PassArgs *ps, int n, BatchStaging *stage, h
     hipError_t e = stage_job_table(stage, jobs.data(), jobs.size() * sizeof(Mfma2DArgs), start, &djobs,
                                    &dstart, stream);
     if (e != hipSuccess) return e;
+    const auto kernel = mfma2d_batch_kernel<DT, SHAPE, r, T, S::V, S::NW, SP>;
     int occ = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, mfma2d_batch_kernel<DT, SHAPE, r, T, V, NW, SP>,
-                                                     64 * NW, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 64 * S::NW, 0);
     if (e != hipSuccess || occ < 1) occ = 1;
     const int slots = occ * (ps[0].num_cu > 0 ? ps[0].num_cu : 256);
     const int total = start.back();
-    hipLaunchKernelGGL((mfma2d_batch_kernel<DT, SHAPE, r, T, V, NW, SP>), dim3(total < slots ? total : slots),
-                       dim3(64 * NW), 0, stream, static_cast<const Mfma2DArgs *>(djobs),
-                       static_cast<const int *>(dstart), (int)jobs.size());
+    hipLaunchKernelGGL(kernel, dim3(total < slots ? total : slots), dim3(64 * S::NW), 0, stream,
+                       static_cast<const Mfma2DArgs *>(djobs), static_cast<const int *>(dstart), (int)jobs.size());
     return hipGetLastError();
+}
+
+// n passes (one per job) of this variant in one persistent launch.
+template <int DT, int SHAPE, int r, int T, bool SP = false>
+hipError_t launch_mfma2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+{
+    if constexpr (use_rows<DT, SHAPE, r, T, SP>())
+        return rows_large(ps, n) ? launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsLarge, SP>(ps, n, stage, stream)
+                                 : launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsSmall, SP>(ps, n, stage, stream);
+    else
+        return launch_mfma2d_batch_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(ps, n, stage, stream);
 }
 
 #define M2(DT, SH, R, T) \
