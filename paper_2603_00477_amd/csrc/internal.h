@@ -99,6 +99,8 @@ struct KernelEntry {
     hipError_t (*launch)(const PassArgs &, hipStream_t);
     // n passes of this variant (different grids) in one persistent launch; may be null
     hipError_t (*launch_batch)(const PassArgs *, int, BatchStaging *, hipStream_t) = nullptr;
+    // up to four output boxes of one pass in one launch; may be null
+    hipError_t (*launch_boxes)(const PassArgs *, int, hipStream_t) = nullptr;
 };
 
 // Kernel registries, one per source file; all_kernel_tables() lists them.

@@ -801,9 +801,69 @@ hipError_t launch_valu2d_batch(const PassArgs *ps, int n, BatchStaging *stage, h
                : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps, n, pick.BY, occ1 * cus, stage, stream);
 }
 
+// Up to kBandBoxes boxes of one pass (the Dirichlet band of a kernel-fused
+// matrix pass) in one launch: the boxes are narrow, so one-column lanes.
+constexpr int kBandBoxes = 4;
+
+template <typename TC, int K>
+struct Valu2DBandArgs {
+    Valu2DJob<TC> g[kBandBoxes];
+    int start[kBandBoxes + 1];  // first workgroup of each box
+    TC w[K];
+};
+
+template <typename TS, typename TC, int SHAPE, int R, int T>
+__global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_band_kernel(
+    Valu2DBandArgs<TC, Valu2DCfg<TS, TC, SHAPE, R, T, 1>::K> a)
+{
+    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, 1>;
+    static_assert(!Cfg::WPTR, "weights in registers");
+    const int wg = blockIdx.x;
+    int j = 0;
+    while (j + 1 < kBandBoxes && a.start[j + 1] <= wg) ++j;
+    const Valu2DJob<TC> g = a.g[j];
+    const int item = valu2d_item(wg - a.start[j]);
+    if (item >= g.nbands * g.nsegs) return;
+    const int seg = item / g.nbands, band = item - seg * g.nbands;
+    TC wk[Cfg::K];
+    load_weights<TC, Cfg::K>(wk, a.w);
+    valu2d_tile<TS, TC, SHAPE, R, T, 1>(g, wk, nullptr, band, seg, threadIdx.x & 63);
+}
+
+// The boxes ps[0..n) of one pass (same grid, weights and boundary).
+template <typename TS, typename TC, int SHAPE, int R, int T>
+hipError_t launch_valu2d_band(const PassArgs *ps, int n, hipStream_t stream)
+{
+    using Cfg = Valu2DCfg<TS, TC, SHAPE, R, T, 1>;
+    if (n < 1 || n > kBandBoxes) return hipErrorInvalidValue;
+    static const int occ = valu2d_occupancy(valu2d_band_kernel<TS, TC, SHAPE, R, T>);
+    Valu2DPick pick;
+    valu2d_try<TS, TC, SHAPE, R, T, 1>(ps, n, occ, ps[0].num_cu > 0 ? ps[0].num_cu : 256, &pick);
+    Valu2DBandArgs<TC, Cfg::K> a;
+    int total = 0;
+    for (int j = 0; j < kBandBoxes; ++j) {
+        const PassArgs &p = ps[j < n ? j : n - 1];
+        a.start[j] = total;
+        valu2d_geometry<TS, TC, SHAPE, R, T, 1>(p, p.tile_rows > 0 ? p.tile_rows : pick.BY, &a.g[j]);
+        if (j < n) total += a.g[j].nwg;
+    }
+    a.start[kBandBoxes] = total;
+    for (int k = 0; k < Cfg::K; ++k) a.w[weight_slot<Cfg, R>(k)] = (TC)ps[0].w[k];
+    hipLaunchKernelGGL((valu2d_band_kernel<TS, TC, SHAPE, R, T>), dim3(total), dim3(64 * kValu2DWaves), 0, stream, a);
+    return hipGetLastError();
+}
+
+// Kernel-fused matrix passes of T >= 2 need their band redone (r = 7 has none).
+template <typename TS, typename TC, int SHAPE, int R, int T>
+constexpr hipError_t (*valu2d_band_launcher())(const PassArgs *, int, hipStream_t)
+{
+    if constexpr (T >= 2 && R <= 3) return &launch_valu2d_band<TS, TC, SHAPE, R, T>;
+    else return nullptr;
+}
+
 #define V2(TS, TC, DT, SH, R, T) \
     {STENCIL_PATH_VALU, DT, SH, 2, R, T, &launch_valu2d<TS, TC, SH, R, T>, \
-     &launch_valu2d_batch<TS, TC, SH, R, T>}
+     &launch_valu2d_batch<TS, TC, SH, R, T>, valu2d_band_launcher<TS, TC, SH, R, T>()}
 #define V2_T(TS, TC, DT, SH, R) \
     V2(TS, TC, DT, SH, R, 1), V2(TS, TC, DT, SH, R, 2), V2(TS, TC, DT, SH, R, 3), V2(TS, TC, DT, SH, R, 4)
 #define V2_R(TS, TC, DT, SH) V2_T(TS, TC, DT, SH, 1), V2_T(TS, TC, DT, SH, 2), V2_T(TS, TC, DT, SH, 3)
