@@ -599,7 +599,10 @@ struct RowsCfg {
     using OP = typename MT::OP;
     using FR = typename MT::FR;
     using ACC = typename MT::ACC;
-    static_assert(MT::KDIM == 32 && !MT::X3, "16-bit operands");
+    static_assert(MT::KDIM == 32, "16-bit operands");
+    // compensated: float32 data split into bf16 hi + lo frames, weights into hi
+    // and lo tables; three products per term
+    static constexpr bool X3 = MT::X3;
     static constexpr int R = r * T, DL = rows_delta(R);
     static constexpr int TR = 16 * V, TC = 16 * NW, NT = 64 * NW;
     static constexpr int LRD = TR + 2 * R;                                  // frame rows
@@ -623,9 +626,37 @@ struct RowsCfg {
     }
     static constexpr int NCH = LCF / 8;                                     // 16-byte chunks per frame row
     static constexpr int NE = (LRD * NCH + NT - 1) / NT;                    // chunks per thread
-    // a 16-byte chunk as a plain vector type (a struct with unions would be
+    static constexpr int FRAME = LRD * PIT;                                 // elements of a staged frame
+    // eight elements as a plain vector type (a struct with unions would be
     // kept in scratch memory when it lives across a loop iteration)
-    typedef unsigned int Chunk __attribute__((ext_vector_type(4)));
+    typedef uint32_t Chunk __attribute__((ext_vector_type(X3 ? 8 : 4)));
+    typedef OP OP8 __attribute__((ext_vector_type(8)));
+
+    __device__ __forceinline__ static Chunk load_chunk(const TS *p)
+    {
+        RawVec<TS, 8> c;
+        c.load_any(p);
+        Chunk v;
+        __builtin_memcpy(&v, c.e, sizeof(Chunk));
+        return v;
+    }
+    // chunk at element `at` of the frame (compensated: of both frames)
+    __device__ __forceinline__ static void put_chunk(const Chunk &v, OP *lb, int at)
+    {
+        if constexpr (X3) {
+            OP8 hi, lo;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float f = __uint_as_float(v[j]);
+                hi[j] = (OP)f;
+                lo[j] = (OP)(f - (float)hi[j]);
+            }
+            *reinterpret_cast<OP8 *>(&lb[at]) = hi;
+            *reinterpret_cast<OP8 *>(&lb[FRAME + at]) = lo;
+        } else {
+            *reinterpret_cast<Chunk *>(&lb[at]) = v;
+        }
+    }
 
     // frame origin in the grid (column a multiple of 8)
     __device__ __forceinline__ static int fr0(const Mfma2DArgs &a, int tile) { return (tile / a.ntc) * TR - R; }
@@ -649,9 +680,7 @@ struct RowsCfg {
             const int e = tid + i * NT;
             const int ec = e < LRD * NCH ? e : LRD * NCH - 1;
             const int rowc = ec / NCH, chc = ec - rowc * NCH;
-            RawVec<TS, 8> c;
-            c.load_any(src + (int64_t)(f0 + rowc) * n1 + g0 + 8 * chc);
-            __builtin_memcpy(&v[i], c.e, sizeof(Chunk));
+            v[i] = load_chunk(src + (int64_t)(f0 + rowc) * n1 + g0 + 8 * chc);
         }
     }
     __device__ __forceinline__ static void write(const Chunk (&v)[NE], OP *lb, int tid)
@@ -660,7 +689,7 @@ struct RowsCfg {
         for (int i = 0; i < NE; ++i) {
             const int e = tid + i * NT;
             const int row = e / NCH, ch = e - row * NCH;
-            if (e < LRD * NCH) *reinterpret_cast<Chunk *>(&lb[row * PIT + 8 * ch]) = v[i];
+            if (e < LRD * NCH) put_chunk(v[i], lb, row * PIT + 8 * ch);
         }
     }
     // edge tiles: a chunk inside
@@ -675,18 +704,18 @@ struct RowsCfg {
         const TS *src = static_cast<const TS *>(a.src);
         const int f0 = fr0(a, tile), g0 = fc0(a, tile), n0 = a.n0, n1 = a.n1;
         const bool periodic = a.periodic != 0;
-        const OP h = to_op<OP>(a.h);
+        const TS hs = to_storage<TS>(a.h);
         constexpr int CB = NE < 8 ? NE : 8;
 #pragma unroll
         for (int e0 = 0; e0 < NE; e0 += CB) {
-            RawVec<TS, 8> v[CB];
+            Chunk v[CB];
 #pragma unroll
             for (int i = 0; i < CB; ++i) {
                 const int e = min(tid + (e0 + i) * NT, LRD * NCH - 1);
                 const int row = e / NCH, gr = f0 + row, gc = g0 + 8 * (e - row * NCH);
                 const int sr = periodic ? wrap(gr, n0) : min(max(gr, 0), n0 - 1);
                 const int sc = periodic ? wrap(gc, n1) : min(max(gc, 0), n1 - 1);
-                if (n1 >= 8) v[i].load_any(src + (int64_t)sr * n1 + min(sc, n1 - 8));
+                v[i] = n1 >= 8 ? load_chunk(src + (int64_t)sr * n1 + min(sc, n1 - 8)) : Chunk(0u);
             }
 #pragma unroll
             for (int i = 0; i < CB; ++i) {
@@ -695,24 +724,24 @@ struct RowsCfg {
                 const int row = e / NCH, gr = f0 + row, c = 8 * (e - row * NCH), gc = g0 + c;
                 const bool rin = gr >= 0 && gr < n0;
                 const int sc = periodic ? wrap(gc, n1) : gc;
-                typedef OP OP8 __attribute__((ext_vector_type(8)));
-                OP8 o;
                 if (c >= LCD) {
-                    o = OP8(OP(0));
-                } else if (sc >= 0 && sc + 8 <= n1 && (rin || periodic)) {
-                    __builtin_memcpy(&o, v[i].e, 16);
-                } else if (!periodic && (!rin || gc + 8 <= 0 || gc >= n1)) {
-                    o = OP8(h);
-                } else {
-                    const TS *rowp = src + (int64_t)(periodic ? wrap(gr, n0) : gr) * n1;
+                    v[i] = Chunk(0u);
+                } else if (!(sc >= 0 && sc + 8 <= n1 && (rin || periodic))) {
+                    TS o[8];
+                    if (!periodic && (!rin || gc + 8 <= 0 || gc >= n1)) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int cj = gc + j;
-                        o[j] = periodic ? to_op<OP>(load_val(rowp[wrap(cj, n1)]))
-                                        : (cj >= 0 && cj < n1 ? to_op<OP>(load_val(rowp[cj])) : h);
+                        for (int j = 0; j < 8; ++j) o[j] = hs;
+                    } else {
+                        const TS *rowp = src + (int64_t)(periodic ? wrap(gr, n0) : gr) * n1;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const int cj = gc + j;
+                            o[j] = periodic ? rowp[wrap(cj, n1)] : (cj >= 0 && cj < n1 ? rowp[cj] : hs);
+                        }
                     }
+                    __builtin_memcpy(&v[i], o, sizeof(Chunk));
                 }
-                *reinterpret_cast<OP8 *>(&lb[row * PIT + c]) = o;
+                put_chunk(v[i], lb, row * PIT + c);
             }
         }
     }
@@ -721,7 +750,7 @@ struct RowsCfg {
     {
         const int lane = tid & 63, wave = tid >> 6;
         const int lg = lane >> 4, ln = lane & 15;
-        const FR *afr = static_cast<const FR *>(a.afrag);
+        const FR *afr = static_cast<const FR *>(a.afrag), *afr_lo = static_cast<const FR *>(a.afrag_lo);
         ACC acc[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = ACC{};
@@ -729,7 +758,7 @@ struct RowsCfg {
         // tile v holds output rows V ln + v, so operand B of (tile v, composite
         // row ar) is data row V ln + (v + ar): one read serves every pair with
         // the same sum, 2R + V reads per k-block in place of V (2R + 1)
-        FR A[V][NKB0];
+        FR A[V][NKB0], Al[X3 ? V : 1][NKB0];
 #pragma unroll
         for (int s = 0; s <= 2 * R + V - 1; ++s) {
             if (s <= 2 * R) {
@@ -739,6 +768,7 @@ struct RowsCfg {
                     if (uses(ar, kb)) {
                         const int f = (rows_frag_offset(SHAPE, r, T, ar) + kb - rows_kk_lo(SHAPE, r, T, ar)) * 64 + lane;
                         A[s % V][kb] = ALDS ? lA[f] : afr[f];
+                        if constexpr (X3) Al[s % V][kb] = ALDS ? lA[NFRAG * 64 + f] : afr_lo[f];
                     }
             }
 #pragma unroll
@@ -747,10 +777,19 @@ struct RowsCfg {
 #pragma unroll
                 for (int v = 0; v < V; ++v) any = any || uses(s - v - R, kb);
                 if (!any) continue;
-                const FR B = *reinterpret_cast<const FR *>(&lb[(V * ln + s) * PIT + colw + 32 * kb]);
+                const OP *bp = &lb[(V * ln + s) * PIT + colw + 32 * kb];
+                const FR B = *reinterpret_cast<const FR *>(bp);
+                const FR Bl = *reinterpret_cast<const FR *>(bp + (X3 ? FRAME : 0));
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    if (uses(s - v - R, kb)) acc[v] = mfma16(A[(s - v + V) % V][kb], B, acc[v]);
+                    if (uses(s - v - R, kb)) {
+                        const int m = (s - v + V) % V;
+                        acc[v] = mfma16(A[m][kb], B, acc[v]);
+                        if constexpr (X3) {
+                            acc[v] = mfma16(A[m][kb], Bl, acc[v]);
+                            acc[v] = mfma16(Al[m][kb], B, acc[v]);
+                        }
+                    }
             }
         }
         // lane (lg, ln) holds row r0 + V ln + v, columns 4 lg .. 4 lg + 3
@@ -788,19 +827,21 @@ __device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int 
     using FR = typename C::FR;
     using OP = typename C::OP;
     constexpr int NFRAG = C::NFRAG, NT = C::NT;
-    __shared__ __attribute__((aligned(16))) OP lb[C::LRD * C::PIT];
-    __shared__ __attribute__((aligned(16))) FR lA[C::ALDS ? NFRAG * 64 : 1];
+    constexpr int NTAB = NFRAG * 64 * (C::X3 ? 2 : 1);  // hi table, then lo table
+    __shared__ __attribute__((aligned(16))) OP lb[C::FRAME * (C::X3 ? 2 : 1)];
+    __shared__ __attribute__((aligned(16))) FR lA[C::ALDS ? NTAB : 1];
     const int tid = threadIdx.x;
     const FR *afr = static_cast<const FR *>(a.afrag);
 
     // A table: loads in flight during the staging
-    constexpr int NAT = C::ALDS ? (NFRAG * 64 + NT - 1) / NT : 1;
+    const FR *afr_lo = static_cast<const FR *>(a.afrag_lo);
+    constexpr int NAT = C::ALDS ? (NTAB + NT - 1) / NT : 1;
     FR ta[NAT];
     if constexpr (C::ALDS) {
 #pragma unroll
         for (int i = 0; i < NAT; ++i) {
             const int e = tid + i * NT;
-            if (e < NFRAG * 64) ta[i] = afr[e];
+            if (e < NTAB) ta[i] = e < NFRAG * 64 ? afr[e] : afr_lo[e - NFRAG * 64];
         }
     }
     if (C::fast(a, tile)) {
@@ -814,22 +855,23 @@ __device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int 
 #pragma unroll
         for (int i = 0; i < NAT; ++i) {
             const int e = tid + i * NT;
-            if (e < NFRAG * 64) lA[e] = ta[i];
+            if (e < NTAB) lA[e] = ta[i];
         }
     }
     __syncthreads();
     C::compute_store(a, tile, lb, lA, tid);
 }
 
-// The 16-bit dense kernels use the row layout when its operand table fits
-// LDS (measured on 16384^2 against the column layout: Box-2D2R bf16 T = 4
-// +5 %, T = 1 +2 %; Box-2D3R bf16 T = 4, 50 fragments read from L2, -41 %);
-// float64/float32, the compensated mode and the sparse instructions use the
-// column layout.  Must agree with mfma_row_layout() (operand upload).
+// The 16-bit and compensated dense kernels use the row layout when its operand
+// table fits LDS (measured on 16384^2 against the column layout: Box-2D2R bf16
+// T = 4 +5 %, T = 1 +2 %, bf16x3 T = 1 / 2 / 4 488 -> 421, 565 -> 496, 855 ->
+// 713 us; Box-2D3R bf16 T = 4, 50 fragments read from L2, -41 %); larger
+// composites, float64/float32 and the sparse instructions use the column
+// layout.  Must agree with mfma_row_layout() (operand upload).
 template <int DT, int SHAPE, int r, int T, bool SP>
 constexpr bool use_rows()
 {
-    return MfmaTypes<DT>::KDIM == 32 && !MfmaTypes<DT>::X3 && !SP && rows_total_frags(SHAPE, r, T) <= 24;
+    return MfmaTypes<DT>::KDIM == 32 && !SP && rows_total_frags(SHAPE, r, T) <= 24;
 }
 
 template <int DT, int SHAPE, int r, int T, int V, int NW, bool SP>
@@ -864,16 +906,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW >= 1
     }
 }
 
-// Tile shapes.  Column layout: 16-bit operands take eight waves side by side
-// (compensated bf16x3 Box-2D2R T = 2 / 4 886 -> 974, 1211 -> 1272 GSt/s against
-// four), float64/float32 four.  Row layout: three stacked tiles of eight waves
-// (48 x 128 points), or, where a pass moves more than the last-level cache
-// holds (256 MB), five tiles of sixteen waves (80 x 256), held to 64 registers
-// so that two workgroups keep 32 waves on a CU: HBM latency is the bound there.
-// bf16 Box-2D2R, us per pass, 3 x 8 | 5 x 8 | 5 x 16:
-//   T = 4: 1024^2 5.1 | 6.1 | 8.4, 4096^2 21.5 | 22.6 | 23.7,
-//          8192^2 74 | 73 | 75, 16384^2 352 | 326 | 292
-//   T = 2: 4096^2 19.3 | 21.2 | 21.9, 16384^2 298 | 282 | 275
+// Tile shapes.  Column layout: 16-bit operands take eight waves side by side,
+// float64/float32 four.  Row layout: three stacked tiles of eight waves
+// (48 x 128 points), or, where a 16-bit pass moves more than the last-level
+// cache holds (256 MB), five tiles of sixteen waves (80 x 256), held to 64
+// registers so that two workgroups keep 32 waves on a CU: HBM latency is the
+// bound there.  Box-2D2R, us per pass, 3 x 8 | 5 x 8 | 5 x 16:
+//   bf16 T = 4: 1024^2 5.1 | 6.1 | 8.4, 4096^2 21.5 | 22.6 | 23.7,
+//               8192^2 74 | 73 | 75, 16384^2 352 | 326 | 292
+//   bf16 T = 2: 4096^2 19.3 | 21.2 | 21.9, 16384^2 298 | 282 | 275
+//   bf16x3 T = 2 (two frames and two tables; column layout 40 and 565):
+//               4096^2 28 | 33 | 42, 16384^2 496 | 504 | 563
 template <int DT>
 struct Mfma2DShape {
     static constexpr int V = 4;
@@ -885,8 +928,10 @@ struct RowsSmall {
 struct RowsLarge {
     static constexpr int V = 5, NW = 16;
 };
-inline bool rows_large(const PassArgs *ps, int n)
+template <int DT>
+bool rows_large(const PassArgs *ps, int n)
 {
+    if (MfmaTypes<DT>::X3) return false;
     double bytes = 0;
     for (int i = 0; i < n; ++i) bytes += 4.0 * ps[i].dims[0] * ps[i].dims[1];  // 2 bytes in, 2 out
     return bytes > 256e6;
@@ -927,7 +972,7 @@ template <int DT, int SHAPE, int r, int T, bool SP = false>
 hipError_t launch_mfma2d(const PassArgs &p, hipStream_t stream)
 {
     if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-        return rows_large(&p, 1) ? launch_mfma2d_shape<DT, SHAPE, r, T, RowsLarge, SP>(p, stream)
+        return rows_large<DT>(&p, 1) ? launch_mfma2d_shape<DT, SHAPE, r, T, RowsLarge, SP>(p, stream)
                                  : launch_mfma2d_shape<DT, SHAPE, r, T, RowsSmall, SP>(p, stream);
     else
         return launch_mfma2d_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(p, stream);
@@ -968,7 +1013,7 @@ template <int DT, int SHAPE, int r, int T, bool SP = false>
 hipError_t launch_mfma2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
     if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-        return rows_large(ps, n) ? launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsLarge, SP>(ps, n, stage, stream)
+        return rows_large<DT>(ps, n) ? launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsLarge, SP>(ps, n, stage, stream)
                                  : launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsSmall, SP>(ps, n, stage, stream);
     else
         return launch_mfma2d_batch_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(ps, n, stage, stream);

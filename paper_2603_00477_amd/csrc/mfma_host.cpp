@@ -118,7 +118,7 @@ void mfma_build_fragments(int shape, int d, int r, const double *w, int steps, i
 }
 
 void mfma_build_row_fragments(int shape, int r, const double *w, int steps, int dtype,
-                              std::vector<uint8_t> *out)
+                              std::vector<uint8_t> *out, std::vector<uint8_t> *lo)
 {
     // Per non-empty k-block of each composite row a (rows -R .. R): 64 lanes
     // x 8 weights; lane l holds A_a[i = l % 16][k = 32 kk + 8 (l / 16) + e].
@@ -129,6 +129,8 @@ void mfma_build_row_fragments(int shape, int r, const double *w, int steps, int 
     std::vector<double> wc;
     compose_dense(shape, 2, r, w, steps, &wc);
     out->assign((size_t)rows_total_frags(shape, r, steps) * 64 * 8 * 2, 0);
+    const bool x3 = dtype == STENCIL_F32_BF16X3;
+    lo->assign(x3 ? out->size() : 0, 0);
     size_t frag = 0;
     for (int a = -R; a <= R; ++a) {
         const int nb = rows_nblk(shape, r, steps, a);
@@ -142,6 +144,10 @@ void mfma_build_row_fragments(int shape, int r, const double *w, int steps, int 
                     const double v = (b >= -R && b <= R) ? wc[(size_t)(a + R) * side + (b + R)] : 0.0;
                     const uint16_t bits = dtype == STENCIL_F16 ? f16_bits(v) : bf16_bits(v);
                     std::memcpy(out->data() + ((frag * 64 + l) * 8 + e) * 2, &bits, 2);
+                    if (x3) {
+                        const uint16_t rest = bf16_bits(v - bf16_value(bits));
+                        std::memcpy(lo->data() + ((frag * 64 + l) * 8 + e) * 2, &rest, 2);
+                    }
                 }
             }
         }
