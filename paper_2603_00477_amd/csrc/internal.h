@@ -112,8 +112,6 @@ const std::vector<KernelEntry> &valu2d_table_x3();  // float storage, FP64 arith
 const std::vector<KernelEntry> &valu3d_fused_kernels();     // stars r <= 3 and boxes r = 1, T = 1..3
 // one-step streaming kernel the table above sends large aligned grids to
 const KernelEntry *valu3d_stream_kernel(int dtype, int shape, int r);
-// one-step float32 Box-3D2R on the row kernel (small grids)
-const KernelEntry &rows3d_box2_kernel();
 const std::vector<KernelEntry> &valu3d_box_kernels();  // boxes r >= 2, one step per pass
 const std::vector<KernelEntry> &valu2d_table_cases();  // r = 7, and r = 1 with T = 5..8
 const std::vector<KernelEntry> &mfma2d_table_cases();  // composite radius 7

@@ -15,16 +15,30 @@
 // plane z the accumulator of output plane z - R is complete: it is stored and
 // the accumulators rotate by one plane.
 //
-// The weights never occupy vector registers: each run of 2R+1 weights
+// The weights do not stay in vector registers: each run of 2R+1 weights
 // w[c][a][-R..R] (one "block") is fetched with scalar loads from the
-// kernel-argument block just before its FMAs (v_fma takes it as the scalar
-// operand).  The fetch of block n+1 is issued before the FMAs of block n
-// (software pipelining).  Scalar loads complete out of order, so a wait for
-// one waits for all; empty volatile asm statements, which keep their relative
-// order, pin the waits: the fetch of block n+1 takes block n's first weight
-// as an operand (it follows the wait for block n), and a statement consuming
-// block n's results follows its FMAs, so the wait for block n+1 comes after
-// them and at most two blocks of weights are live in scalar registers.
+// kernel-argument block just before its FMAs.  The fetch of block n+1 is
+// issued before the FMAs of block n (software pipelining).  Scalar loads
+// complete out of order, so a wait for one waits for all; empty volatile asm
+// statements, which keep their relative order, pin the waits: the fetch of
+// block n+1 takes block n's first weight as an operand (it follows the wait
+// for block n), and a statement consuming block n's results follows its FMAs,
+// so the wait for block n+1 comes after them and at most two blocks of weights
+// are live in scalar registers.
+//
+// The first and last 2R planes of a segment serve fewer than 2R+1 output
+// planes.  They run c by c and leave out the c whose output plane lies outside
+// the segment, so a segment of BZ planes computes BZ * (2R+1)^3 weights per
+// point and not (BZ + 2R) * (2R+1)^3: short segments, which a small grid needs
+// to fill the chip, cost only the extra plane loads.  Time per step with every
+// plane run in full on four workgroups per CU, and now, in us on random
+// periodic grids: float32 Box-3D2R 64^3 34 and 10, 97^3 37 and 19, 200^3 68 and
+// 52, 512^3 549 and 513; Box-3D3R 64^3 78 and 17, 115^3 81 and 36, 200^3 202
+// and 112, 512^3 1496 and 1162; float64 Box-3D2R 97^3 31 and 24, 512^3 880 and
+// 850; Box-3D3R 64^3 60 and 20, 200^3 187 and 160, 512^3 1845 and 1802.  (Run c
+// by c throughout, the rows are read from LDS 2R+1 times: float32 Box-3D3R
+// 512^3 1573 us against 1040.  Variants here and below were compared on grids
+// of zeros, which the card computes some 10 % faster at 512^3.)
 //
 // Contributions to one output arrive in canonical order (c, then a, then b
 // ascending), as in the oracle.
@@ -69,6 +83,13 @@ struct Box3Cfg {
     static constexpr int WIN = W + 2 * R;                // window row length
     static constexpr int WINV = (WIN + VE - 1) / VE;     // 16-byte reads per window row
 };
+
+// Waves per SIMD the kernels are compiled for.  Float32 r = 2 needs 81 vector
+// registers, one more than six waves leave: held to 80 (12 bytes of scratch),
+// 512^3 takes 437 us instead of 458 (seven waves: 557).  The 16-row tiles of
+// small grids gain nothing (200^3 48.6 us, 47.9 without).
+template <typename TC, int R, int TY>
+constexpr int box3_waves = sizeof(TC) == 4 && R == 2 && TY == 32 ? 6 : 4;
 
 // Weights in the constant address space: loads through it are scalar.
 template <typename TC>
@@ -171,62 +192,88 @@ __device__ __forceinline__ void box3_tile(const Box3Args<TC, Box3Cfg<TS, TC, R, 
                 for (int e = 0; e < VE; ++e) row[v * VE + e] = t.e[e];
             }
         };
-        // blocks n = 0 .. Q*Q-1 in order (a = n / Q, c = n % Q - R): the
-        // weights of block n+1 are fetched while block n runs
-        // Scalar loads complete out of order, so any wait for one waits for all:
-        // the fetch of block n+1 takes block n's first weight as an operand,
-        // which puts it after the wait for block n's weights (and it then runs
-        // under block n's FMAs).
-        // The ordering dependency goes through the base pointer, so each
-        // block's offset stays a compile-time immediate of its scalar loads
-        // (an opaque offset cost scalar address arithmetic per block:
-        // Box-3D2R 512^3 f32 / f64 250 -> 258, 155 -> 162 GSt/s without it).
-        auto fetch_w = [&](int n, TC *wv, TC after) {
-            const int wrow = ((n % Q) * Q + n / Q) * Q;  // canonical index of w[c][a][-R]
-            WPtr<TC> p = wk;
-            if constexpr (sizeof(TC) == 4 && R == 2) asm volatile("" : "+s"(p) : "v"(after));  // W(n)
-            else asm volatile("" : "+s"(p) : "s"(after));
-#pragma unroll
-            for (int b = 0; b < Q; ++b) {
-                wv[b] = p[wrow + b];
-                // float32 r = 2: FMAs run faster on vector-register operands (one
-                // move each, +15 %); r = 3 keeps them scalar (the moves' registers
-                // cost a wave of occupancy, -9 %)
-                if constexpr (sizeof(TC) == 4 && R == 2) asm volatile("" : "+v"(wv[b]));
-            }
-        };
-        TC wcur[Q], wnxt[Q];
-        fetch_w(0, wcur, TC(0));
-        TC rr[WY][WINV * VE];  // window rows a .. a+WY-1 (row a+i serves output row i)
-#pragma unroll
-        for (int n = 0; n < Q * Q; ++n) {
-            const int a = n / Q, c = n % Q - R;
-            if (n == 0) {
+        // Window rows a .. a+WY-1 of the thread (row a+i serves output row i).
+        auto next_row = [&](TC(&rr)[WY][WINV * VE], int a) {
+            if (a == 0) {
 #pragma unroll
                 for (int i = 0; i < WY; ++i) load_row(rr[i], i);
-            } else if (c == -R) {
+            } else {
 #pragma unroll
                 for (int i = 0; i + 1 < WY; ++i)
 #pragma unroll
                     for (int e = 0; e < WINV * VE; ++e) rr[i][e] = rr[i + 1][e];
                 load_row(rr[WY - 1], a + WY - 1);
             }
-            if (n + 1 < Q * Q) fetch_w(n + 1, wnxt, wcur[0]);
+        };
+        // Scalar loads complete out of order, so any wait for one waits for all:
+        // the fetch of a block takes the previous block's first weight as an
+        // operand, which puts it after the wait for that block's weights (and it
+        // then runs under that block's FMAs).
+        // The ordering dependency goes through the base pointer, so each
+        // block's offset stays a compile-time immediate of its scalar loads
+        // (an opaque offset cost scalar address arithmetic per block:
+        // Box-3D2R 512^3 f32 / f64 250 -> 258, 155 -> 162 GSt/s without it).
+        auto fetch_w = [&](int a, int c, TC *wv, TC after) {
+            WPtr<TC> p = wk;
+            asm volatile("" : "+s"(p) : "s"(after));
+#pragma unroll
+            for (int b = 0; b < Q; ++b) wv[b] = p[((c + R) * Q + a) * Q + b];
+        };
+        auto block = [&](const TC *wv, const TC(&rr)[WY][WINV * VE], int c) {
             const int m = R - c;  // accumulator plane of output z - c
+            // float32 FMAs run faster on vector-register operands, one move a
+            // weight included.  The move stands at the use: at the fetch it
+            // waited for the scalar load there and then (512^3 float32 Box-3D2R
+            // 468 -> 437 us; Box-3D3R 1440 with scalar operands -> 1074).
+            TC wu[Q];
+#pragma unroll
+            for (int b = 0; b < Q; ++b) {
+                wu[b] = wv[b];
+                if constexpr (sizeof(TC) == 4) asm volatile("" : "+v"(wu[b]));
+            }
 #pragma unroll
             for (int i = 0; i < WY; ++i)
 #pragma unroll
                 for (int b = 0; b < Q; ++b)
 #pragma unroll
-                    for (int j = 0; j < W; ++j) acc[m][i][j] = fma_c(wcur[b], rr[i][j + b], acc[m][i][j]);
-            // E(n): block n's results exist before W(n+2), whose operand
-            // needs block n+1's weights: the wait for them follows block n
+                    for (int j = 0; j < W; ++j) acc[m][i][j] = fma_c(wu[b], rr[i][j + b], acc[m][i][j]);
+            // the block's results exist before the fetch after next, whose
+            // operand needs the next block's weights: the wait for them
+            // follows this block
 #pragma unroll
             for (int i = 0; i < WY; ++i)
 #pragma unroll
                 for (int j = 0; j < W; ++j) asm volatile("" ::"v"(acc[m][i][j]));
+        };
+        TC wcur[Q], wnxt[Q];
+        TC rr[WY][WINV * VE];
+        if (k >= 2 * R && k < nk - 2 * R) {
+            // all 2R+1 output planes: blocks n = 0 .. Q*Q-1, a = n / Q and
+            // c = n % Q - R, each window row read once
+            fetch_w(0, -R, wcur, TC(0));
 #pragma unroll
-            for (int b = 0; b < Q; ++b) wcur[b] = wnxt[b];
+            for (int n = 0; n < Q * Q; ++n) {
+                if (n % Q == 0) next_row(rr, n / Q);
+                if (n + 1 < Q * Q) fetch_w((n + 1) / Q, (n + 1) % Q - R, wnxt, wcur[0]);
+                block(wcur, rr, n % Q - R);
+#pragma unroll
+                for (int b = 0; b < Q; ++b) wcur[b] = wnxt[b];
+            }
+        } else {
+            const int z = zb + k;
+#pragma unroll
+            for (int c = -R; c <= R; ++c) {
+                if (z - c < z0 || z - c >= z1) continue;
+                fetch_w(0, c, wcur, TC(0));
+#pragma unroll
+                for (int a = 0; a < Q; ++a) {
+                    next_row(rr, a);
+                    if (a + 1 < Q) fetch_w(a + 1, c, wnxt, wcur[0]);
+                    block(wcur, rr, c);
+#pragma unroll
+                    for (int b = 0; b < Q; ++b) wcur[b] = wnxt[b];
+                }
+            }
         }
         // accumulator plane 0 is output plane zb + k - R
         const int zo = zb + k - R;
@@ -266,7 +313,8 @@ __device__ __forceinline__ void box3_tile(const Box3Args<TC, Box3Cfg<TS, TC, R, 
 }
 
 template <typename TS, typename TC, int R, int W, int WY, int TX, int TY>
-__global__ __launch_bounds__(TX *TY) void valu3d_box_kernel(
+__global__ __launch_bounds__(TX *TY)
+__attribute__((amdgpu_waves_per_eu(box3_waves<TC, R, TY>))) void valu3d_box_kernel(
     Box3Args<TC, Box3Cfg<TS, TC, R, W, WY, TX, TY>::K> a)
 {
     using Cfg = Box3Cfg<TS, TC, R, W, WY, TX, TY>;
@@ -295,9 +343,28 @@ __global__ __launch_bounds__(TX *TY) void valu3d_box_batch_kernel(
     int j = 0;
     for (int item = xcd_remap(blockIdx.x, gridDim.x); item < total; item += gridDim.x) {
         while (j + 1 < njobs && tile_start[j + 1] <= item) ++j;
-        const Args a = jobs[j];
-        const WPtr<TC> wk = (WPtr<TC>)((const __attribute__((address_space(4))) char *)(jobs + j) +
-                                       offsetof(Args, w));
+        // geometry by scalar loads (copied through the generic pointer, float32
+        // r = 2 took 106 vector registers and not 96)
+        using JPtr = const __attribute__((address_space(4))) Args *;
+        const JPtr job = (JPtr)(jobs + __builtin_amdgcn_readfirstlane(j));
+        Args a;
+        a.src = job->src;
+        a.dst = job->dst;
+        a.n0 = job->n0;
+        a.n1 = job->n1;
+        a.n2 = job->n2;
+        a.oz0 = job->oz0;
+        a.oz1 = job->oz1;
+        a.oy0 = job->oy0;
+        a.oy1 = job->oy1;
+        a.ox0 = job->ox0;
+        a.ox1 = job->ox1;
+        a.BZ = job->BZ;
+        a.nty = job->nty;
+        a.ntx = job->ntx;
+        a.periodic = job->periodic;
+        a.h = job->h;
+        const WPtr<TC> wk = &job->w[0];
         box3_tile<TS, TC, R, W, WY, TX, TY>(a, wk, item - tile_start[j], lds);
     }
 }
@@ -347,32 +414,33 @@ bool box3_args(const PassArgs &p, int BZ, Box3Args<TC, Box3Cfg<TS, TC, R, W, WY,
     return true;
 }
 
-// Planes per segment of a launch over n passes.  A workgroup takes BZ + 2R
-// plane iterations; one costs a latency that grows with the weight stream
-// (about 2000 cycles for 125 weights) and the FMAs of the waves that share a
-// SIMD.  The estimate is that times the rounds over the resident workgroups.
-// Measured at 64^3..512^3 against every length from 4 planes up, the choice is
-// 0.6 % behind the best on average, 3 % at most; a fixed target of four
-// workgroups per CU and at least 4R planes had been up to 43 % behind
-// (float32 Box-3D2R 64^3 34.5 -> 23.3, 200^3 67.5 -> 57.9 us with the tiles
-// below; Box-3D3R 64^3 78 -> 45, 200^3 200 -> 163).
+// Planes per segment of a launch over n passes.  A workgroup computes BZ planes'
+// worth of FMAs and loads 2R more planes.  One plane costs a latency (weight
+// stream, LDS, barrier) and the FMAs of the waves that share a SIMD; the
+// estimate is that times the rounds over the resident workgroups, over
+// segments of up to 16R planes (longer ones have too few workgroups to even
+// out: float32 Box-3D2R 512^3 103 planes 545 us, 27 planes 462).  Fitted to
+// every length from 1 plane up at 48^3..512^3 (float32 and float64, r = 2 and
+// 3): the choice is 1 % behind the best on average, 8 % at most.
 template <typename TC, int R, int W, int WY, int TX, int TY>
 int box3_segment(const PassArgs *ps, int n, int slots_per_cu, int cus)
 {
     using Cfg = Box3Cfg<TC, TC, R, W, WY, TX, TY>;
-    static const int kSegs[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,  16, 20,
-                                24, 28, 32, 40, 48, 64, 96, 128, 192, 256};
-    const double wave = (sizeof(TC) == 8 ? 4.0 : 3.0) * Cfg::K * W * WY;
-    const double latency = 2000.0 * (R == 2 ? 1.0 : 2.0);
+    static const int kPlanes[] = {1,  2,  3,  4,  5,  6,  7,  8,  9,  10, 11, 12,
+                                  13, 14, 16, 18, 20, 22, 24, 28, 32, 37, 43, 48};
+    constexpr bool F64 = sizeof(TC) == 8;
+    const double wave = 2.5 * Cfg::K * W * WY;
+    const double latency = !F64 ? 4000.0 : (R == 2 ? 1000.0 : 3000.0);
     const int nw = TX * TY / 64, slots = cus * slots_per_cu;
     auto extent = [](const PassArgs &p, int i) { return std::max(p.region_hi[i] - p.region_lo[i], 0); };
     int dmax = 1;
     for (int i = 0; i < n; ++i) dmax = std::max(dmax, extent(ps[i], 0));
     int best = dmax, last = 0;
     double best_cost = -1.0;
-    for (int segs : kSegs) {
-        const int BZ = (dmax + segs - 1) / segs;
-        if (BZ == last) break;
+    for (int most : kPlanes) {
+        if (most > 16 * R) break;
+        const int segs = (dmax + most - 1) / most, BZ = (dmax + segs - 1) / segs;
+        if (BZ == last) continue;
         last = BZ;
         double items = 0;
         for (int i = 0; i < n; ++i)
@@ -382,7 +450,7 @@ int box3_segment(const PassArgs *ps, int n, int slots_per_cu, int cus)
         auto plane = [&](double resident) { return latency + wave * (double)(int64_t)((resident * nw + 3) / 4); };
         double rounds = full * plane(slots_per_cu);
         if (rest > 0) rounds += plane((double)(int64_t)((rest + cus - 1) / cus));
-        const double cost = (BZ + 1.6 * R) * rounds;
+        const double cost = (BZ + (F64 ? 0.5 : 0.3) * R) * rounds;
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = BZ;
@@ -453,55 +521,38 @@ hipError_t launch_box3_batch_cfg(const PassArgs *ps, int n, BatchStaging *stage,
 }
 
 // Tiles: one 16-byte vector (float32 4 points, float64 2) and one row per
-// thread, 32 columns of points: 8 x 32 threads in float32, 16 x 16 in float64.
-// Measured on 384^3 / 512^3 periodic grids against 2-row and 3-row threads, the
-// one-row threads need 70-96 VGPRs and keep 5-7 waves per SIMD, which hides
-// the LDS and scalar-load latencies best (5-15 % faster).  Against 64-column
-// tiles (16 x 32 and 16 x 16 threads in float32, 16 x 32 in float64), each with
-// its best segments, the 32-column ones waste less of the last tile and
-// balance finer: Box-3D2R float32 200^3 65.9 -> 57.9 us, 512^3 470 -> 461;
-// Box-3D3R float32 200^3 184 -> 163; Box-3D2R float64 512^3 701 -> 671.
-template <typename TC, int R>
+// thread, 32 columns of points.  Two and three rows per thread are 5-15 %
+// slower: the one-row threads need 68-107 VGPRs and keep 4-7 waves per SIMD,
+// which hides the LDS and scalar-load latencies best.  64-column tiles waste
+// more of the last tile.  16 rows; float32 grids of more than 160^3 points
+// take 32, which stage fewer halo rows (float32 Box-3D2R 97^3 17.4 us with 16
+// rows, 19.7 with 32; 512^3 453 and 437.  Box-3D3R 97^3 31.9 and 36.2, 512^3
+// 1048 and 1040.  float64 Box-3D2R 97^3 22.5, 512^3 648 with 16 rows; with 8
+// rows 21.9 and 671).  A batch runs on 16 rows in one launch.
+template <typename TC>
 struct Box3Shape {
     static constexpr int W = sizeof(TC) == 8 ? 2 : 4;
     static constexpr int TX = sizeof(TC) == 8 ? 16 : 8;
-    static constexpr int TY = sizeof(TC) == 8 ? 16 : 32;
+    static constexpr int TY = 16;
 };
-
-// Float32 r = 2 grids of up to 160^3 points go to the row kernel of
-// valu3d_fused.hip, whose 125 weights stay in vector registers: with one wave
-// per SIMD the weight stream's latency is the bound here (Box-3D2R 64^3 23.3
-// vs 14.0 us, 97^3 32.7 vs 18.6, 160^3 36.8 vs 31.5; 200^3 57.9 vs 60.2,
-// 256^3 80 vs 95).
-template <typename TC, int R>
-bool box3_small(const PassArgs &p)
-{
-    if (sizeof(TC) != 4 || R != 2) return false;
-    int64_t points = 1;
-    for (int i = 0; i < 3; ++i) points *= std::max(p.region_hi[i] - p.region_lo[i], 0);
-    return points <= (int64_t)160 * 160 * 160;
-}
 
 template <typename TS, typename TC, int R>
 hipError_t launch_box3(const PassArgs &p, hipStream_t stream)
 {
-    using S = Box3Shape<TC, R>;
-    if (box3_small<TC, R>(p)) return rows3d_box2_kernel().launch(p, stream);
+    using S = Box3Shape<TC>;
+    if constexpr (sizeof(TC) == 4) {
+        int64_t points = 1;
+        for (int i = 0; i < 3; ++i) points *= std::max(p.region_hi[i] - p.region_lo[i], 0);
+        if (points > (int64_t)160 * 160 * 160) return launch_box3_cfg<TS, TC, R, S::W, 1, S::TX, 32>(p, stream);
+    }
     return launch_box3_cfg<TS, TC, R, S::W, 1, S::TX, S::TY>(p, stream);
 }
 
 template <typename TS, typename TC, int R>
 hipError_t launch_box3_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    using S = Box3Shape<TC, R>;
-    std::vector<PassArgs> small, other;
-    for (int i = 0; i < n; ++i) (box3_small<TC, R>(ps[i]) ? small : other).push_back(ps[i]);
-    hipError_t e = hipSuccess;
-    if (!other.empty())
-        e = launch_box3_batch_cfg<TS, TC, R, S::W, 1, S::TX, S::TY>(other.data(), (int)other.size(), stage, stream);
-    if (e == hipSuccess && !small.empty())
-        e = rows3d_box2_kernel().launch_batch(small.data(), (int)small.size(), stage, stream);
-    return e;
+    using S = Box3Shape<TC>;
+    return launch_box3_batch_cfg<TS, TC, R, S::W, 1, S::TX, S::TY>(ps, n, stage, stream);
 }
 
 #define B3(TS, TC, DT, R) \

@@ -392,7 +392,7 @@ struct Rows3DShape {
                               : T == 1 || (F64 && T == 2) ? 1
                               : F64                       ? 0
                                                           : (R == 2 && T == 3 ? 1 : 2);
-    static constexpr int MINW = BOX && R == 2 ? 2 : F64 && (R == 3 || (R == 2 && T > 1)) ? 1 : 4;
+    static constexpr int MINW = F64 && (R == 3 || (R == 2 && T > 1)) ? 1 : 4;
 };
 
 // One in-plane box of a launch: planes, rows and columns to write.
@@ -653,12 +653,6 @@ const std::vector<KernelEntry> &valu3d_fused_kernels()
         F3_S(float, STENCIL_F32),
     };
     return table;
-}
-
-const KernelEntry &rows3d_box2_kernel()
-{
-    static const KernelEntry entry = F3(float, STENCIL_F32, STENCIL_BOX, 2, 1);
-    return entry;
 }
 
 }  // namespace stl

@@ -73,9 +73,8 @@ def test_rows3d_batch_of_uneven_grids(stl, dt):
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("r", [2, 3])
 def test_large_box_beyond_the_small_grid_rule(stl, dt, r):
-    """Boxes r >= 2 over 160^3 points (float32 r = 2 below that takes the row
-    kernel): ragged 32-column tiles and segments, sampled windows, and a batch
-    with a small grid."""
+    """Boxes r >= 2 over 160^3 points (float32 takes 32-row tiles there): ragged
+    tiles and segments, sampled windows, and a batch with a small grid."""
     import torch
     from oracle import core as ocore
     import stencil_inputs as si
@@ -101,6 +100,21 @@ def test_large_box_beyond_the_small_grid_rule(stl, dt, r):
     torch.cuda.synchronize()
     for a, b in zip(outs, batch):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("r", [2, 3])
+@pytest.mark.parametrize("boundary", ["dirichlet", "periodic"])
+def test_large_box_segment_lengths(stl, dt, r, boundary):
+    """The first and last 2r planes of a segment compute part of the weights:
+    segments of one plane, of 2r (no full plane) and beyond, a ragged last one."""
+    dims = (4 * r + 7, 33, 37)
+    u0, u0r, t, w = case_inputs("box", 3, r, dims, dt, seed=6400 + r)
+    ref = oracle("box", 3, r, w, u0, 1, boundary, 0.5)
+    for planes in (1, 2, 2 * r, 2 * r + 1, 4 * r + 3, 4 * r + 7):
+        p = stl.Plan("box", 3, r, w, dims, T=1, dtype=dt, path="valu", boundary=boundary, halo=0.5,
+                     tile_rows=planes)
+        assert rel_inf(run_gpu(p, t, 1), ref) <= TOL[dt], planes
 
 
 @pytest.mark.parametrize("shape,r", [("star", 2), ("box", 1)])
