@@ -181,3 +181,39 @@ def test_batch_groups_3d_and_mfma(stl):
             ref = oracle(shape, d, r, w, u0r, steps[k], bnd)
             bound = lowp_bound(dt, omodel.K_fused(shape, d, r, T), -(-steps[k] // T), float(np.max(np.abs(u0r))))
             assert float(np.max(np.abs(got - ref))) <= bound, spec[k]
+
+
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_batch_of_many_variants_is_ordered_with_its_stream(stl, own_stream):
+    """Enough work of different kernels to be spread over several streams: it
+    starts after what the caller's stream did before (the inputs are made there
+    just before the call), ends before what the stream does next, and equals
+    each job run alone bit for bit.  Two jobs share an input."""
+    import torch
+    jobs = [("box", 3, 3, 1, "f32", (90, 97, 101), 3), ("box", 3, 2, 1, "f64", (97, 90, 88), 3),
+            ("star", 3, 2, 2, "f32", (130, 120, 125), 6), ("star", 3, 2, 2, "f32", (64, 120, 125), 5),
+            ("box", 2, 3, 2, "f64", (1500, 1501), 5), ("box", 2, 2, 1, "bf16", (1024, 1000), 4),
+            ("star", 2, 1, 3, "f16", (700, 900), 7), ("box", 2, 2, 1, "f32", (333, 1000), 0),
+            ("box", 3, 1, 2, "f32", (130, 120, 125), 5)]
+    stream = torch.cuda.Stream() if own_stream else torch.cuda.current_stream()
+    plans, base = [], []
+    for k, (shape, d, r, T, dt, dims, steps) in enumerate(jobs):
+        u0, u0r, t, w = case_inputs(shape, d, r, dims, dt, seed=7300 + k)
+        plans.append(stl.Plan(shape, d, r, w, dims, T=T, dtype=dt, boundary="periodic" if k % 2 else "dirichlet",
+                              path="valu"))
+        base.append(t.cuda())
+    steps = [j[6] for j in jobs]
+    torch.cuda.synchronize()
+    for rep in range(3):
+        with torch.cuda.stream(stream):
+            ins = [x * (0.5 + rep) for x in base]
+            ins[8] = ins[2]
+            outs = [torch.full_like(x, -7.0) for x in ins]
+            stl.run_batch(plans, ins, outs, steps)
+            got = [y * 1.0 for y in outs]
+        stream.synchronize()
+        for k, (p, x) in enumerate(zip(plans, ins)):
+            alone = torch.empty_like(x)
+            p.run(x, alone, steps[k])
+            torch.cuda.synchronize()
+            assert torch.equal(got[k], alone), (rep, jobs[k])
