@@ -87,12 +87,13 @@ MfmaLayout mfma_layout(int shape, int d, int r, int steps, int dtype)
     return L;
 }
 
-// Skirt recomputation of the VALU kernels' fused tiles: executed / useful
-// FMAs.  2D: a wave's band of 64 W columns (W = 16-byte vector) keeps
+// Skirt recomputation of the VALU path's fused tiles: executed / useful FMAs,
+// for one reference layout per case.  The launchers pick lane widths and tiles
+// per grid; the model keeps these fixed values (they are part of its output),
+// which depend on the problem alone.  2D: a wave's band of 64 W columns (W = 16-byte vector) keeps
 // 64 W - 2 E outputs, E = r T rounded up to W.  3D: an in-plane tile of
 // (TY WY) x (TX W) points keeps (TY WY - 2 EY) x (TX W - 2 EX), EY = r T for
-// fused passes (one-step passes stage their halo: no skirt); the thread tiles
-// are those the 3D launcher picks.
+// fused passes (one-step passes stage their halo: no skirt).
 static double valu_halo_factor(int shape, int d, int r, int T, int dtype)
 {
     const int D = dtype_bytes(dtype);

@@ -76,8 +76,8 @@ struct Valu2DCfg {
     static constexpr int U = Q * ((4 + Q - 1) / Q);
     // input rows in flight: U for small Q; for r = 7 (Q = 15, compute-bound,
     // 225 or 29 FMAs per input value) 3 rows, a divisor of U, so the ring
-    // slot of row k is k mod P at compile time and 48 VGPRs stay free
-    // 32-byte lanes (float64 at T = 2) prefetch one row: their rows take
+    // slot of row k is k mod P at compile time and 48 VGPRs stay free.
+    // 32-byte lanes (float64, four columns) prefetch one row: their rows take
     // twice the arithmetic, and the registers go to the wider accumulators
     static constexpr int P = sizeof(TS) * W > 16 ? 1
                              : (U <= 8 ? U : (U % 3 == 0 ? 3 : (U % 4 == 0 ? 4 : (U % 5 == 0 ? 5 : U))));
@@ -89,10 +89,9 @@ struct Valu2DCfg {
     // measured).  Float64 at T = 1 streams them too (Box-2D3R: 88 instead of
     // 236 VGPRs; +9 % measured at 10240^2, equal at 8192^2).  Float32 at T = 2
     // keeps them pinned in VGPRs (632 vs 478 GSt/s measured) unless they need
-    // more than 128 dwords (r = 7: 225 weights).  Float64 at T = 2 runs
-    // 32-byte lanes, which stream them too: each weight then serves four
-    // columns, and the freed registers hold the wider accumulators at two
-    // waves per SIMD.
+    // more than 128 dwords (r = 7: 225 weights).  Float64 lanes of four columns
+    // stream them too: each weight then serves four columns, and the freed
+    // registers hold the wider accumulators at two waves per SIMD.
     // Single-column lanes hold few accumulators and keep them in registers
     // (a streamed column would serve 2R+1 FMAs only), r = 7 excepted.
     static constexpr bool WPTR = SHAPE == STENCIL_BOX && sizeof(TC) * K > 192 &&
@@ -104,6 +103,15 @@ struct Valu2DCfg {
     // GSt/s; at T = 2 the per-stage order is as fast or faster (Box-2D3R
     // float64 353 vs 344).
     static constexpr bool WCOL = WPTR && T >= 3;
+    // The first contribution to an output multiplies instead of adding to a
+    // zeroed accumulator: two moves less per output value and stage, and fewer
+    // registers (Star-2D2R T = 4 272 -> 246, which fits two waves per SIMD).
+    // Time per pass before and after in float64: Star-2D2R T = 4 4096^2 35 %,
+    // 8192^2 20 % faster, Star-2D3R T = 3 8192^2 18 %, Box-2D3R T = 2 8192^2
+    // 356 -> 341 us.  One- and two-column lanes, and float32, get schedules
+    // with more registers from it and are 5-15 % slower at 512^2; Box-2D3R
+    // T = 4, which spans both register files, 8 % at 8192^2.
+    static constexpr bool MUL_FIRST = sizeof(TC) == 8 && W == 4 && !(WCOL && T * Q > 24);
 };
 
 // Weights in constant memory (scalar loads).
@@ -183,6 +191,13 @@ __device__ __forceinline__ void assemble_window(const TC (&own)[W], TC (&win)[W 
         const int t = W + m;
         win[R + W + m] = lane_read(own[t % W], (lane + t / W) * 4);
     }
+}
+
+template <bool MUL_FIRST, typename TC>
+__device__ __forceinline__ TC accumulate(TC w, TC x, TC sum, bool first)
+{
+    if constexpr (MUL_FIRST) return first ? w * x : fma_c(w, x, sum);
+    else return fma_c(w, x, sum);
 }
 
 // One tile (column band x row segment) of one pass, run by one wave.
@@ -328,7 +343,8 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                             const int q = ((u - ao + R) % Q + Q) % Q;
 #pragma unroll
                             for (int j = 0; j < W; ++j)
-                                acc[s - 1][q][j] = fma_c(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j]);
+                                acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
+                                                                              ao == -R && bo == -R);
                         }
                     }
                     // this column's FMAs complete before the wait for the next
@@ -364,7 +380,8 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                                 const int q = ((u - ao + R) % Q + Q) % Q;
 #pragma unroll
                                 for (int j = 0; j < W; ++j)
-                                    acc[s - 1][q][j] = fma_c(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j]);
+                                    acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
+                                                                              ao == -R && bo == -R);
                             }
                             // this column's FMAs complete before the wait for the
                             // next column's weights (which the fetch after next
@@ -387,12 +404,14 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                                     const TC wv = wk[(ao + R) * (2 * R + 1) + (bo + R)];
 #pragma unroll
                                     for (int j = 0; j < W; ++j)
-                                        acc[s - 1][q][j] = fma_c(wv, win[j + bo + R], acc[s - 1][q][j]);
+                                        acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wv, win[j + bo + R], acc[s - 1][q][j],
+                                                                                      ao == -R && bo == -R);
                                 } else if (ao != 0 && bo == 0) {
                                     const TC wv = wk[star_axis_index<SHAPE, R>(0, ao)];
 #pragma unroll
                                     for (int j = 0; j < W; ++j)
-                                        acc[s - 1][q][j] = fma_c(wv, win[j + R], acc[s - 1][q][j]);
+                                        acc[s - 1][q][j] =
+                                            accumulate<Cfg::MUL_FIRST>(wv, win[j + R], acc[s - 1][q][j], ao == -R);
                                 } else if (ao == 0) {
                                     const TC wv = bo == 0 ? wk[0] : wk[star_axis_index<SHAPE, R>(1, bo)];
 #pragma unroll
@@ -426,8 +445,9 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                         }
                     }
                 }
+                if constexpr (!Cfg::MUL_FIRST)
 #pragma unroll
-                for (int j = 0; j < W; ++j) acc[s - 1][qc][j] = TC(0);
+                    for (int j = 0; j < W; ++j) acc[s - 1][qc][j] = TC(0);
                 // window of this stage's row for stage s+1 at the next iteration
                 if (s < T) assemble_window<TC, W, R>(outv, wins[s], lane);
             }
