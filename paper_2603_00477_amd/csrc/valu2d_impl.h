@@ -103,15 +103,17 @@ struct Valu2DCfg {
     // GSt/s; at T = 2 the per-stage order is as fast or faster (Box-2D3R
     // float64 353 vs 344).
     static constexpr bool WCOL = WPTR && T >= 3;
-    // The first contribution to an output multiplies instead of adding to a
-    // zeroed accumulator: two moves less per output value and stage, and fewer
-    // registers (Star-2D2R T = 4 272 -> 246, which fits two waves per SIMD).
+    // The first contribution to an output adds to a constant zero instead of a
+    // zeroed accumulator (a product alone would keep the sign of a zero, which
+    // must not depend on the lane width): two moves less per output value and
+    // stage, and fewer registers (Star-2D2R T = 4 272 -> 246, which fits two
+    // waves per SIMD).
     // Time per pass before and after in float64: Star-2D2R T = 4 4096^2 35 %,
     // 8192^2 20 % faster, Star-2D3R T = 3 8192^2 18 %, Box-2D3R T = 2 8192^2
     // 356 -> 341 us.  One- and two-column lanes, and float32, get schedules
     // with more registers from it and are 5-15 % slower at 512^2; Box-2D3R
     // T = 4, which spans both register files, 8 % at 8192^2.
-    static constexpr bool MUL_FIRST = sizeof(TC) == 8 && W == 4 && !(WCOL && T * Q > 24);
+    static constexpr bool FIRST_FROM_ZERO = sizeof(TC) == 8 && W == 4 && !(WCOL && T * Q > 24);
 };
 
 // Weights in constant memory (scalar loads).
@@ -193,11 +195,10 @@ __device__ __forceinline__ void assemble_window(const TC (&own)[W], TC (&win)[W 
     }
 }
 
-template <bool MUL_FIRST, typename TC>
+template <bool FIRST_FROM_ZERO, typename TC>
 __device__ __forceinline__ TC accumulate(TC w, TC x, TC sum, bool first)
 {
-    if constexpr (MUL_FIRST) return first ? w * x : fma_c(w, x, sum);
-    else return fma_c(w, x, sum);
+    return fma_c(w, x, FIRST_FROM_ZERO && first ? TC(0) : sum);
 }
 
 // One tile (column band x row segment) of one pass, run by one wave.
@@ -343,7 +344,7 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                             const int q = ((u - ao + R) % Q + Q) % Q;
 #pragma unroll
                             for (int j = 0; j < W; ++j)
-                                acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
+                                acc[s - 1][q][j] = accumulate<Cfg::FIRST_FROM_ZERO>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
                                                                               ao == -R && bo == -R);
                         }
                     }
@@ -380,7 +381,7 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                                 const int q = ((u - ao + R) % Q + Q) % Q;
 #pragma unroll
                                 for (int j = 0; j < W; ++j)
-                                    acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
+                                    acc[s - 1][q][j] = accumulate<Cfg::FIRST_FROM_ZERO>(wcur[ao + R], win[j + bo + R], acc[s - 1][q][j],
                                                                               ao == -R && bo == -R);
                             }
                             // this column's FMAs complete before the wait for the
@@ -404,14 +405,14 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                                     const TC wv = wk[(ao + R) * (2 * R + 1) + (bo + R)];
 #pragma unroll
                                     for (int j = 0; j < W; ++j)
-                                        acc[s - 1][q][j] = accumulate<Cfg::MUL_FIRST>(wv, win[j + bo + R], acc[s - 1][q][j],
+                                        acc[s - 1][q][j] = accumulate<Cfg::FIRST_FROM_ZERO>(wv, win[j + bo + R], acc[s - 1][q][j],
                                                                                       ao == -R && bo == -R);
                                 } else if (ao != 0 && bo == 0) {
                                     const TC wv = wk[star_axis_index<SHAPE, R>(0, ao)];
 #pragma unroll
                                     for (int j = 0; j < W; ++j)
                                         acc[s - 1][q][j] =
-                                            accumulate<Cfg::MUL_FIRST>(wv, win[j + R], acc[s - 1][q][j], ao == -R);
+                                            accumulate<Cfg::FIRST_FROM_ZERO>(wv, win[j + R], acc[s - 1][q][j], ao == -R);
                                 } else if (ao == 0) {
                                     const TC wv = bo == 0 ? wk[0] : wk[star_axis_index<SHAPE, R>(1, bo)];
 #pragma unroll
@@ -445,7 +446,7 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
                         }
                     }
                 }
-                if constexpr (!Cfg::MUL_FIRST)
+                if constexpr (!Cfg::FIRST_FROM_ZERO)
 #pragma unroll
                     for (int j = 0; j < W; ++j) acc[s - 1][qc][j] = TC(0);
                 // window of this stage's row for stage s+1 at the next iteration

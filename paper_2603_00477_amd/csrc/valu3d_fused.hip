@@ -262,17 +262,18 @@ __device__ __forceinline__ void rows3d_tile(const Rows3DArgs<TC, K> &a, const TC
                             if (ao < -R || ao > R) continue;
                             TC &o = acc[s - 1][q][i];
                             // the first contribution (c = -R, first row and
-                            // column) starts the sum
+                            // column) starts the sum, from zero: a product alone
+                            // would keep the sign of a zero
                             if constexpr (SHAPE == STENCIL_BOX) {
 #pragma unroll
                                 for (int bo = -R; bo <= R; ++bo) {
                                     const TC wv_ = wk[((c + R) * Q + (ao + R)) * Q + (bo + R)];
-                                    o = (c == -R && ao == -R && bo == -R) ? wv_ * row[0] : fma_c(wv_, row[bo + R], o);
+                                    o = fma_c(wv_, row[bo + R], c == -R && ao == -R && bo == -R ? TC(0) : o);
                                 }
                             } else if (c != 0) {  // z arm: own column only
                                 if (ao != 0) continue;
                                 const TC wv_ = wk[star3r_index<R>(0, c)];
-                                o = c == -R ? wv_ * row[R] : fma_c(wv_, row[R], o);
+                                o = fma_c(wv_, row[R], c == -R ? TC(0) : o);
                             } else if (ao != 0) {  // y arm
                                 o = fma_c(wk[star3r_index<R>(1, ao)], row[R], o);
                             } else {  // x arm with the centre
