@@ -460,76 +460,55 @@ int run_one(stencil_plan_s *p, const void *in, void *out, int64_t steps, hipStre
     return STENCIL_OK;
 }
 
-// Batched runs: the jobs are dealt to lanes, the caller's stream and up to
-// three side streams that fork from it and join it again.  In a lane, round j
-// issues pass j of every job that has one.  Passes of one round that share a
-// kernel variant go out as one persistent batched launch (workgroups pull
-// tiles of all those grids from one list); variants without a batched form go
-// out one by one, and the Dirichlet band fix-ups of kernel-fused MFMA passes
-// follow the round's launches.  Each job's passes stay in stream order and
-// ping-pong exactly as in run_one, so every result is bit-identical to running
-// the job alone.
+// Batched runs: round j issues pass j of every job that has one.  Passes of
+// one round that share a kernel variant go out as one persistent batched
+// launch (workgroups pull tiles of all those grids from one list); variants
+// without a batched form go out one by one, and the Dirichlet band fix-ups
+// of kernel-fused MFMA passes follow the round's launches.  Each job's
+// passes stay in stream order and ping-pong exactly as in run_one, so every
+// result is bit-identical to running the job alone.
 std::mutex g_batch_mu;
 
-// Side streams of one device, made at the first batch that uses them and kept.
-// Used under g_batch_mu; a wait refers to the record made just before it, so
-// the events serve the next call too.
-constexpr int kSideLanes = 3;
-constexpr double kLaneMinWork = 5e8;  // multiply-adds outside the largest lane
-struct BatchLanes {
-    hipStream_t side[kSideLanes] = {};
-    hipEvent_t fork = nullptr, joined[kSideLanes] = {};
-    bool ready = false;
-
-    hipError_t init()
-    {
-        if (ready) return hipSuccess;
-        hipError_t e = hipSuccess;
-        if (!fork) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-        for (int i = 0; i < kSideLanes && e == hipSuccess; ++i) {
-            if (!side[i]) e = hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking);
-            if (e == hipSuccess && !joined[i]) e = hipEventCreateWithFlags(&joined[i], hipEventDisableTiming);
-        }
-        ready = e == hipSuccess;
-        return e;
-    }
-    ~BatchLanes()
-    {
-        // process teardown: the runtime may already be gone, errors are ignored
-        for (int i = 0; i < kSideLanes; ++i) {
-            if (side[i]) (void)hipStreamDestroy(side[i]);
-            if (joined[i]) (void)hipEventDestroy(joined[i]);
-        }
-        if (fork) (void)hipEventDestroy(fork);
-    }
-};
-
-// One lane's jobs (indices into the batch), in `stream`.
-int run_lane(const std::vector<int> &jobs, const std::vector<std::vector<PassDesc>> &sched,
-             const stencil_plan_t *plans, const void *const *ins, void *const *outs, BatchStaging &stage,
-             hipStream_t stream)
+int run_batch(int n, const stencil_plan_t *plans, const void *const *ins, void *const *outs,
+              const int64_t *steps, hipStream_t stream)
 {
+    std::lock_guard<std::mutex> lock(g_batch_mu);
+    static std::map<int, BatchStaging> stages;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    BatchStaging &stage = stages[dev];
+    hipError_t e = stage.begin(stream);
+    if (e != hipSuccess) return fail(STENCIL_ERR_HIP, std::string("batch staging: ") + hipGetErrorString(e));
+    // the slot is marked busy until the stream passes this point, also when a
+    // launch below fails after earlier ones were queued
+    struct SlotRelease {
+        BatchStaging &s;
+        hipStream_t st;
+        ~SlotRelease() { (void)s.end(st); }
+    } release{stage, stream};
+
+    std::vector<std::vector<PassDesc>> sched((size_t)n);
     size_t rounds = 0;
-    std::vector<const void *> src;
-    for (int i : jobs) {
-        src.push_back(ins[i]);
+    for (int i = 0; i < n; ++i) {
+        if (steps[i] == 0) {
+            e = hipMemcpyAsync(outs[i], ins[i], grid_bytes(plans[i]), hipMemcpyDeviceToDevice, stream);
+            if (e != hipSuccess) return fail(STENCIL_ERR_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
+            continue;
+        }
+        sched[i] = schedule(plans[i], steps[i]);
         rounds = std::max(rounds, sched[i].size());
-        if (!sched[i].empty()) continue;
-        const hipError_t e = hipMemcpyAsync(outs[i], ins[i], grid_bytes(plans[i]), hipMemcpyDeviceToDevice, stream);
-        if (e != hipSuccess) return fail(STENCIL_ERR_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
     }
+    std::vector<const void *> src(ins, ins + n);
     struct Fixup {
         stencil_plan_s *p;
         int t;
         const void *src;
         void *dst;
     };
-    hipError_t e;
     for (size_t j = 0; j < rounds; ++j) {
         std::map<const KernelEntry *, std::vector<PassArgs>> groups;
         std::vector<Fixup> fixups;  // Dirichlet bands, after the passes they correct
-        for (size_t q = 0; q < jobs.size(); ++q) {
-            const int i = jobs[q];
+        for (int i = 0; i < n; ++i) {
             const auto &ps = sched[i];
             if (j >= ps.size()) continue;
             stencil_plan_s *p = plans[i];
@@ -538,9 +517,9 @@ int run_lane(const std::vector<int> &jobs, const std::vector<std::vector<PassDes
             const PassDesc &pd = ps[j];
             if (!pd.k) return fail(STENCIL_ERR_UNSUPPORTED, "no kernel for a pass");
             PassArgs a = base_args(p, pd.t);
-            a.src = src[q];
+            a.src = src[i];
             a.dst = dst;
-            src[q] = dst;
+            src[i] = dst;
             if (is_mfma_path(pd.path)) {
                 a.afrag = p->afrag[pd.t];
                 a.afrag_lo = p->afrag_lo[pd.t];
@@ -566,136 +545,6 @@ int run_lane(const std::vector<int> &jobs, const std::vector<std::vector<PassDes
         }
     }
     return STENCIL_OK;
-}
-
-// No job writes what another reads or writes, so their order is free.
-bool jobs_independent(int n, const stencil_plan_t *plans, const void *const *ins, void *const *outs)
-{
-    struct Span {
-        uintptr_t lo, hi;
-        bool write;
-    };
-    std::vector<Span> spans;
-    for (int i = 0; i < n; ++i) {
-        const size_t bytes = grid_bytes(plans[i]);
-        spans.push_back({(uintptr_t)ins[i], (uintptr_t)ins[i] + bytes, false});
-        spans.push_back({(uintptr_t)outs[i], (uintptr_t)outs[i] + bytes, true});
-    }
-    std::sort(spans.begin(), spans.end(), [](const Span &a, const Span &b) { return a.lo < b.lo; });
-    uintptr_t end = 0, wend = 0;  // of all spans so far, and of the written ones
-    for (const Span &s : spans) {
-        if (s.lo < wend || (s.write && s.lo < end)) return false;
-        end = std::max(end, s.hi);
-        if (s.write) wend = std::max(wend, s.hi);
-    }
-    return true;
-}
-
-// Jobs per lane; none where one lane is as good.  Jobs whose first pass is the
-// same kernel stay together (their passes share launches); such groups go,
-// largest first, to the lane with the least work.  Work is points times
-// pattern points times steps.  Lanes pay where launches are too small to fill
-// the chip or end in a tail, and forking and joining costs about 50 us, so the
-// lanes beside the first must hold 5e8 multiply-adds (some 100 us).  Measured,
-// one lane and these: float32, 16 jobs (2D to 2048^2, 3D to 192^3) 540 -> 357
-// us, 8 jobs (1024^2, 96^3; 1.1e9 beside the largest) 496 -> 359, 64 jobs
-// (512^2, 64^3) 1679 -> 1176; below the line, always dealt: 8 jobs (256^2,
-// 32^3; 4e6) 100 -> 143 back to back, 4 jobs of 4.6-us launches 149 -> 204.
-// Two side streams instead of three: 32 jobs 914 -> 1073.
-std::vector<std::vector<int>> deal_lanes(int n, const std::vector<std::vector<PassDesc>> &sched,
-                                         const stencil_plan_t *plans, const int64_t *steps)
-{
-    struct Group {
-        double work = 0.0;
-        std::vector<int> jobs;
-    };
-    std::map<const KernelEntry *, Group> by_kernel;
-    for (int i = 0; i < n; ++i) {
-        Group &g = by_kernel[sched[i].empty() ? nullptr : sched[i][0].k];
-        g.jobs.push_back(i);
-        g.work += (double)plans[i]->npts * (double)plans[i]->K * (double)steps[i];
-    }
-    std::vector<Group> groups;
-    for (auto &g : by_kernel) groups.push_back(std::move(g.second));
-    // equal work: by the first job, not by where the kernel table lies
-    std::sort(groups.begin(), groups.end(), [](const Group &a, const Group &b) {
-        return a.work != b.work ? a.work > b.work : a.jobs[0] < b.jobs[0];
-    });
-    std::vector<std::vector<int>> lanes(std::min<size_t>(groups.size(), 1 + kSideLanes));
-    std::vector<double> load(lanes.size(), 0.0);
-    for (Group &g : groups) {
-        const size_t l = std::min_element(load.begin(), load.end()) - load.begin();
-        lanes[l].insert(lanes[l].end(), g.jobs.begin(), g.jobs.end());
-        load[l] += std::max(g.work, 1.0);
-    }
-    double rest = 0.0;
-    for (size_t l = 1; l < lanes.size(); ++l) rest += load[l];
-    if (rest < kLaneMinWork) lanes.clear();
-    return lanes;
-}
-
-int run_batch(int n, const stencil_plan_t *plans, const void *const *ins, void *const *outs,
-              const int64_t *steps, hipStream_t stream)
-{
-    std::lock_guard<std::mutex> lock(g_batch_mu);
-    static std::map<int, BatchStaging> stages;
-    static std::map<int, BatchLanes> side_lanes;
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    BatchStaging &stage = stages[dev];
-    hipError_t e = stage.begin(stream);
-    if (e != hipSuccess) return fail(STENCIL_ERR_HIP, std::string("batch staging: ") + hipGetErrorString(e));
-    // the slot is marked busy until the stream passes this point, also when a
-    // launch below fails after earlier ones were queued
-    struct SlotRelease {
-        BatchStaging &s;
-        hipStream_t st;
-        ~SlotRelease() { (void)s.end(st); }
-    } release{stage, stream};
-
-    std::vector<std::vector<PassDesc>> sched((size_t)n);
-    std::vector<int> all;
-    for (int i = 0; i < n; ++i) {
-        all.push_back(i);
-        if (steps[i] > 0) sched[i] = schedule(plans[i], steps[i]);  // else a copy
-    }
-    // one lane while a graph is captured, and for dependent jobs
-    std::vector<std::vector<int>> lanes;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (n > 1 && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
-        capture == hipStreamCaptureStatusNone && jobs_independent(n, plans, ins, outs))
-        lanes = deal_lanes(n, sched, plans, steps);
-    BatchLanes &side = side_lanes[dev];
-    if (lanes.size() < 2 || side.init() != hipSuccess) {
-        (void)hipGetLastError();
-        return run_lane(all, sched, plans, ins, outs, stage, stream);
-    }
-
-    e = hipEventRecord(side.fork, stream);
-    if (e != hipSuccess) return fail(STENCIL_ERR_HIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
-    int rc = STENCIL_OK;
-    size_t forked = 0;
-    for (size_t l = 1; l < lanes.size() && rc == STENCIL_OK; ++l) {
-        e = hipStreamWaitEvent(side.side[l - 1], side.fork, 0);
-        if (e != hipSuccess) {
-            rc = fail(STENCIL_ERR_HIP, std::string("hipStreamWaitEvent: ") + hipGetErrorString(e));
-            break;
-        }
-        forked = l;
-        rc = run_lane(lanes[l], sched, plans, ins, outs, stage, side.side[l - 1]);
-    }
-    if (rc == STENCIL_OK) rc = run_lane(lanes[0], sched, plans, ins, outs, stage, stream);
-    // join what was forked, also after a failed launch: the caller's stream
-    // (and the staging slot's release) comes after all of the batch
-    for (size_t l = 1; l <= forked; ++l) {
-        e = hipEventRecord(side.joined[l - 1], side.side[l - 1]);
-        if (e == hipSuccess) e = hipStreamWaitEvent(stream, side.joined[l - 1], 0);
-        if (e != hipSuccess) {
-            (void)hipStreamSynchronize(side.side[l - 1]);
-            if (rc == STENCIL_OK) rc = fail(STENCIL_ERR_HIP, std::string("lane join: ") + hipGetErrorString(e));
-        }
-    }
-    return rc;
 }
 
 bool overlap(const void *a, const void *b, size_t n)
