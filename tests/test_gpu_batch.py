@@ -217,3 +217,62 @@ def test_batch_of_many_variants_is_ordered_with_its_stream(stl, own_stream):
             p.run(x, alone, steps[k])
             torch.cuda.synchronize()
             assert torch.equal(got[k], alone), (rep, jobs[k])
+
+
+def _independent_streams(torch, sleep):
+    """Two streams of which one runs on while the other is busy (streams that
+    share a hardware queue wait for each other whatever runs on them)."""
+    busy = torch.cuda.Stream()
+    x = torch.zeros(64, device="cuda")
+    for _ in range(8):
+        free = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(sleep)
+            held = torch.cuda.Event()
+            held.record()
+        with torch.cuda.stream(free):
+            x.add_(1)
+        free.synchronize()
+        if not held.query():
+            return busy, free
+    pytest.skip("no two independent streams")
+
+
+def test_batches_on_two_streams_are_independent(stl):
+    """A batch on one stream ends while a batch on another stream still waits
+    behind that stream's earlier work (a sleep of fixed length)."""
+    import torch
+    sleep = 200_000_000  # some 80 ms
+    jobs = [("box", 3, 3, 1, "f32", (90, 97, 101), 2), ("star", 3, 2, 2, "f32", (130, 120, 125), 4),
+            ("box", 2, 3, 2, "f64", (1500, 1501), 4), ("box", 3, 2, 1, "f64", (97, 90, 88), 2)]
+    sides = []
+    for s in range(2):
+        plans, ins = [], []
+        for k, (shape, d, r, T, dt, dims, steps) in enumerate(jobs):
+            u0, u0r, t, w = case_inputs(shape, d, r, dims, dt, seed=7400 + 10 * s + k)
+            plans.append(stl.Plan(shape, d, r, w, dims, T=T, dtype=dt, path="valu"))
+            ins.append(t.cuda())
+        sides.append((plans, ins, [torch.empty_like(x) for x in ins]))
+    steps = [j[6] for j in jobs]
+    alone = []
+    for plans, ins, outs in sides:
+        alone.append([torch.empty_like(x) for x in ins])
+        for p, x, y, n in zip(plans, ins, alone[-1], steps):
+            p.run(x, y, n)
+        stl.run_batch(plans, ins, outs, steps)  # scratch grids and staging exist from here on
+    busy, free = _independent_streams(torch, sleep)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(sleep)
+        held = torch.cuda.Event()
+        held.record()
+        stl.run_batch(*sides[0], steps)
+    with torch.cuda.stream(free):
+        stl.run_batch(*sides[1], steps)
+    free.synchronize()
+    assert not held.query()
+    torch.cuda.synchronize()
+    for (plans, ins, outs), ref in zip(sides, alone):
+        for a, b in zip(ref, outs):
+            assert torch.equal(a, b)
