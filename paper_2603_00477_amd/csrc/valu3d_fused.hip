@@ -406,38 +406,55 @@ struct Rows3DPick {
 };
 
 // Waves per workgroup (4 or 8) and planes per segment of a launch over n
-// boxes.  A workgroup takes BZ + 2RT + T plane iterations (the lead-in ones,
-// where later stages idle, count 0.6); one costs about 1500 cycles of latency
-// (barrier, LDS, the next plane's loads) and the arithmetic of the waves that
-// share a SIMD.  The estimate is that times the rounds over the resident
-// workgroups.  Small grids come out with segments of a few planes that put
-// work on every CU (97^3 float32 Star-3D1R T = 2: 7 planes 9.8 us, 33 planes
-// 25), large ones with segments that amortise the lead-in planes in whole
-// rounds (512^3 Star-3D2R float64 T = 3: 171 planes 738 us, 128 871).  r = 1
-// and one-step passes are near the memory bound at large sizes and gain from
-// neighbouring tiles running close in time: at most 16 R T planes (512^3
-// Star-3D1R float64 T = 2: 171 planes 549 us, 32 502).  Over ten variants at 64^3..512^3 the choice is
-// 0.6 % behind the best of all measured (4.. 512-plane) segments on average,
-// 8 % at most.
+// boxes, by an estimate in cycles of a launch's time: the root of the squares
+// of its issue time and its bytes' time.
+//   issue: a workgroup takes BZ + 2RT + T plane iterations (the lead-in ones,
+//     where later stages idle, count 0.2) and the worth of 3.7 more to start;
+//     one costs a latency (barrier, LDS, the next plane's loads) and the
+//     arithmetic of the waves that share a SIMD; times the rounds over the
+//     resident workgroups.
+//   bytes: one read and one write per point, and a fifth of what the tiles'
+//     margins and lead-in planes read again (caches hold the rest), at 1600 a
+//     cycle.
+// Lengths from one plane to 512 are tried, whatever the height (a tall grid
+// once fell through to a single segment: 6000 x 32^2 float32 Star-3D1R 3284 us
+// instead of 48).  Small grids come out with segments of a few planes that put
+// work on every CU (48^3 float32 Star-3D1R T = 2: 1 plane 5.4 us, 4 planes 7.9;
+// 97^3: 3 planes 9.7, 33 planes 25), large ones with segments that amortise
+// the lead-in planes in whole rounds (512^3 Star-3D2R float64 T = 3: 171 planes
+// 738 us, 128 871).  r = 1 and one-step passes are near the memory bound at
+// large sizes and gain from neighbouring tiles running close in time: at most
+// 16 R T planes (512^3 Star-3D1R float64 T = 2: 171 planes 549 us, 32 502).
+// Fitted to 11 variants in float32 and float64 on 62 grids (32^3..512^3, flat,
+// tall, and at random): the choice is 1 % behind the best of all measured
+// lengths on average, 24 % at most (float64 r = 3 one-step passes of
+// 128 x 640^2).
 template <typename Cfg, typename TC, int SHAPE, int R, int T, int WY>
 Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const int (&occ)[2])
 {
-    const double wave = T * WY * ((sizeof(TC) == 8 ? 4.0 : 2.5) * Cfg::K + 4.0 * (2 * R * (sizeof(TC) / 4) + 8));
-    static const int kSegs[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,  16, 20,
-                                24, 28, 32, 40, 48, 64, 96, 128, 192, 256};
+    constexpr bool F64 = sizeof(TC) == 8;
+    const double wave = T * WY * ((F64 ? 5.5 : 2.0) * Cfg::K + 3.2 * (2 * R * (sizeof(TC) / 4) + 16));
+    const double latency = (F64 ? 950.0 : 600.0) + 400.0 * T;
+    static const int kPlanes[] = {1,  2,  3,  4,  5,  6,  7,  8,  9,  10, 11, 12, 13, 14,  16,  18,  20, 22,
+                                  24, 28, 32, 37, 43, 48, 52, 57, 64, 74, 86, 103, 128, 171, 256, 512};
     int dmax = 1;
-    for (int i = 0; i < n; ++i) dmax = std::max(dmax, boxes[i].d0);
+    double points = 0;
+    for (int i = 0; i < n; ++i) {
+        dmax = std::max(dmax, boxes[i].d0);
+        points += (double)boxes[i].d0 * boxes[i].d1 * boxes[i].d2;
+    }
     Rows3DPick best{kRowsMaxWaves, dmax};
     double best_cost = -1.0;
     for (int v = 0; v < 2; ++v) {
         const int nw = v ? kRowsMaxWaves : kRowsMinWaves, BY = nw * WY - 2 * Cfg::SK;
         const int slots = cus * occ[v];
         int last = 0;
-        for (int segs : kSegs) {
-            int BZ = fixed_bz > 0 ? fixed_bz : (dmax + segs - 1) / segs;
-            if (BZ == last) break;
+        for (int most : kPlanes) {
+            if ((R == 1 || T == 1) && most > 16 * R * T) break;
+            const int segs = (dmax + most - 1) / most;
+            const int BZ = fixed_bz > 0 ? fixed_bz : (dmax + segs - 1) / segs;
+            if (BZ == last) continue;
             last = BZ;
-            if ((R == 1 || T == 1) && fixed_bz <= 0 && BZ > 16 * R * T) continue;
             double items = 0;
             for (int i = 0; i < n; ++i)
                 items += (double)((boxes[i].d0 + BZ - 1) / BZ) * ((boxes[i].d1 + BY - 1) / BY) *
@@ -446,11 +463,15 @@ Rows3DPick rows3d_pick(const Box3 *boxes, int n, int fixed_bz, int cus, const in
             const double rest = items - full * slots;
             auto plane = [&](double resident) {  // cycles of a plane iteration
                 const double perSimd = (double)(int64_t)((resident * nw + 3) / 4);
-                return 1500.0 + wave * perSimd;
+                return latency + wave * perSimd;
             };
             double rounds = full * plane(occ[v]);
             if (rest > 0) rounds += plane((double)(int64_t)((rest + cus - 1) / cus));
-            const double cost = (std::min(BZ, dmax) + 0.6 * (2 * R * T + T)) * rounds;
+            const int BZe = std::min(BZ, dmax);
+            const double issue = (BZe + 0.2 * (2 * R * T + T) + 3.7) * rounds;
+            const double read = items * (BZe + 2 * R * T) * (nw * WY + 2 * R) * 64;
+            const double bytes = sizeof(TC) * (2 * points + 0.2 * std::max(read - points, 0.0)) / 1600.0;
+            const double cost = issue * issue + bytes * bytes;
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = {nw, BZ};

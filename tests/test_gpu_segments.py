@@ -1,0 +1,72 @@
+"""Segments of a pass (planes of the 3D row kernel, rows of the 2D kernel) on
+grids whose swept axis is long: many of them, alone and beside small grids.
+Tolerances as for the other VALU kernels: FP64 relative max-norm error <= 1e-12,
+FP32 <= 1e-5."""
+import pytest
+
+from gpu_util import case_inputs, oracle, rel_inf, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-12, "f32": 1e-5}
+
+
+@pytest.fixture(scope="module")
+def stl():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_00477_amd as stl
+    stl.lib()
+    return stl
+
+
+def _time(run, reps=5):
+    """Shortest time of a call, ms."""
+    import torch
+    best = float("inf")
+    for _ in range(reps):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        run()
+        t1.record()
+        torch.cuda.synchronize()
+        best = min(best, t0.elapsed_time(t1))
+    return best
+
+
+@pytest.mark.parametrize("shape,r,T", [("star", 1, 1), ("box", 1, 1), ("star", 2, 1), ("star", 1, 2)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_tall_grid(stl, shape, r, T, dt):
+    """9000 planes are swept at the rate of 3000 (one segment for all of them
+    would take some 60 times as long), alone and in a batch beside a small
+    grid, and have the oracle's values."""
+    import torch
+    plans, ins, outs = [], [], []
+    for k, dims in enumerate([(9000, 20, 30), (3000, 20, 30), (40, 20, 30)]):
+        u0, u0r, t, w = case_inputs(shape, 3, r, dims, dt, seed=7700 + k)
+        plans.append(stl.Plan(shape, 3, r, w, dims, T=T, dtype=dt, path="valu", halo=0.5))
+        ins.append(t.cuda())
+        outs.append(torch.empty_like(ins[-1]))
+        plans[-1].run(ins[-1], outs[-1], T)
+        torch.cuda.synchronize()
+        ref = oracle(shape, 3, r, w, u0, T, "dirichlet", 0.5)
+        assert rel_inf(outs[-1].to(torch.float64).cpu().numpy(), ref) <= TOL[dt], dims
+    steps = 20 * T
+    tall, less = (_time(lambda: p.run(x, y, steps)) for p, x, y in list(zip(plans, ins, outs))[:2])
+    assert tall <= 12 * less, (tall, less)
+    alone = [y.clone() for y in outs]
+    both = _time(lambda: stl.run_batch(plans[::2], ins[::2], outs[::2], [steps] * 2))
+    assert both <= 12 * less, (both, less)
+    assert torch.equal(outs[0], alone[0])
+
+
+@pytest.mark.parametrize("shape,r,T", [("star", 1, 3), ("star", 2, 2), ("star", 3, 1), ("box", 1, 2)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_segments_of_one_to_three_planes(stl, shape, r, T, dt):
+    for dims in [(7, 33, 70), (2, 20, 40), (12, 9, 130)]:
+        u0, u0r, t, w = case_inputs(shape, 3, r, dims, dt, seed=7750 + dims[0])
+        ref = oracle(shape, 3, r, w, u0, T, "periodic")
+        for planes in (1, 2, 3):
+            p = stl.Plan(shape, 3, r, w, dims, T=T, dtype=dt, path="valu", boundary="periodic", tile_rows=planes)
+            assert rel_inf(run_gpu(p, t, T), ref) <= TOL[dt], (dims, planes)
