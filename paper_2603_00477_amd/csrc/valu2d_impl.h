@@ -633,26 +633,38 @@ int valu2d_occupancy(K kernel)
 //     each of them.  A workgroup puts one wave on every SIMD of its CU, so the
 //     busiest CU's workgroups, not the average, count (8192^2 float32
 //     Star-2D3R T = 4: 504 workgroups = 2 per CU 171 us, 576 279).
+//     Float64 lanes of four columns whose accumulators span both register files
+//     (Box-2D3R T = 4, one wave per SIMD) take 1.3 times their instructions:
+//     without it they were picked from 3000 x 7000 up, 8192^2 968 us where
+//     two-column lanes take 802.
 //   bytes: one read and one write per point, the read grown by the skirt and
 //     the halo rows, at about 1800 bytes a cycle from HBM or 3500 from the
-//     last-level cache (256 MB).
-// Fitted to 216 variants and sizes (72 variants, 300^2..8192^2, 45 choices
-// each): the choice is 2.4 % behind the best measured on average.
+//     last-level cache (256 MB); 1.12 times as long for 32-byte lanes on rows
+//     that are no whole number of 128-byte lines (float64 Star-2D1R T = 3
+//     3000 x 7000: two columns 69 us, four 83; 6000^2: 152 and 137).
+// Fitted to 2800 variants and sizes (76 variants, 256^2..8192^2, flat, tall and
+// at random, some 40 choices each): the choice is 2.5 % behind the best
+// measured on average.
 template <typename Cfg, typename TS, typename TC, int SHAPE, int R, int T, int W>
 struct Valu2DCost {
+    static constexpr double stretch()
+    {
+        return sizeof(TC) == 8 && W == 4 && Cfg::WCOL && T * Cfg::Q > 24 ? 1.3 : 1.0;
+    }
     static double issue(int64_t nwg, int BY, int occ, int cus)
     {
         const double row =
-            T * (W * ((sizeof(TC) == 8 ? 4.5 : 2.5) * Cfg::K + 32) + 12.0 * 2 * R * (sizeof(TC) / 4)) + 20;
+            stretch() * (T * (W * ((sizeof(TC) == 8 ? 4.5 : 2.5) * Cfg::K + 32) + 12.0 * 2 * R * (sizeof(TC) / 4)) + 20);
         const double latency = 1500 + (Cfg::WPTR ? 100.0 * Cfg::Q * (T >= 3 ? 1 : T) : 0.0);
         auto resident = [&](int64_t k) { return latency + row * (k > 1 ? k - 0.4 : k); };
         const int64_t per_cu = (nwg + cus - 1) / cus, full = per_cu / occ, rest = per_cu % occ;
         return (BY + 2 * R * T + T) * (full * resident(occ) + (rest ? resident(rest) : 0.0));
     }
-    static double memory(double points, int BY, int BX)
+    static double memory(double points, int BY, int BX, bool whole_lines)
     {
         const double grow = (1.0 + 2.0 * R * T / BY) * Cfg::NCW / BX;
-        return points * sizeof(TS) * (1.0 + grow) / (2 * points * sizeof(TS) > 256e6 ? 1800.0 : 3500.0);
+        const double wide = sizeof(TS) * W > 16 && !whole_lines ? 1.12 : 1.0;
+        return wide * points * sizeof(TS) * (1.0 + grow) / (2 * points * sizeof(TS) > 256e6 ? 1800.0 : 3500.0);
     }
 };
 
@@ -678,6 +690,7 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
     int64_t bands = 0;
     int hmax = 1, bx = 1;
     double points = 0, area = 0;  // area: bands x rows
+    bool whole_lines = true;      // rows of whole 128-byte lines
     Valu2DJob<TC> g;
     for (int i = 0; i < n; ++i) {
         const int H = ps[i].region_hi[0] - ps[i].region_lo[0];
@@ -688,6 +701,7 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
         points += valu2d_points(ps[i]);
         hmax = std::max(hmax, H);
         bx = g.BX;
+        whole_lines = whole_lines && (int64_t)g.n1 * (int)sizeof(TS) % 128 == 0;
     }
     auto workgroups = [&](int BY) {
         int64_t items = 0;
@@ -706,7 +720,7 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
     if (n == 1 && ps[0].tile_rows > 0) {  // the caller's segment length
         const int BY = ps[0].tile_rows;
         consider(BY, false, std::max(Cost::issue(workgroups(BY), std::min(BY, hmax), occ, cus),
-                                     Cost::memory(points, BY, bx)));
+                                     Cost::memory(points, BY, bx, whole_lines)));
         return;
     }
     static const int kPerCu[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32};
@@ -727,7 +741,7 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
         // shortest ones where their issue time is within 1.4 of the bytes'.
         const bool streams = k == 32 && W == (sizeof(TS) == 8 ? 2 : 4) && 2 * points * sizeof(TS) > 256e6 &&
                              issue < 1.4 * 2 * points * sizeof(TS) / 1800.0;
-        consider(BY, streams, std::max(issue, Cost::memory(points, BY, bx)));
+        consider(BY, streams, std::max(issue, Cost::memory(points, BY, bx, whole_lines)));
     }
     // fewer bands of work than one workgroup per CU: whole columns
     if (best->cost < 0) consider(hmax, false, Cost::issue(workgroups(hmax), hmax, occ, cus));

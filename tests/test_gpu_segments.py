@@ -70,3 +70,21 @@ def test_segments_of_one_to_three_planes(stl, shape, r, T, dt):
         for planes in (1, 2, 3):
             p = stl.Plan(shape, 3, r, w, dims, T=T, dtype=dt, path="valu", boundary="periodic", tile_rows=planes)
             assert rel_inf(run_gpu(p, t, T), ref) <= TOL[dt], (dims, planes)
+
+
+def test_float64_lanes_within_the_registers(stl):
+    """Box-2D3R float64 fused four deep keeps to lanes whose accumulators leave
+    room for two waves per SIMD: a pass takes some 2.3 times one of T = 2 (2.8
+    with four columns per lane and one wave)."""
+    import torch
+    dims = (8192, 8192)
+    K = 49
+    w = [1.0 / K] * K
+    x = torch.rand(dims, device="cuda", dtype=torch.float64)
+    y = torch.empty_like(x)
+    ms = {}
+    for T in (2, 4):
+        p = stl.Plan("box", 2, 3, w, dims, T=T, dtype="f64", path="valu")
+        p.run(x, y, 2 * T)
+        ms[T] = _time(lambda: p.run(x, y, 2 * T))
+    assert ms[4] <= 2.55 * ms[2], ms
