@@ -732,6 +732,9 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
         if (n == 1 && segs < 1) continue;
         int BY = n == 1 ? (int)((hmax + segs - 1) / segs) : (int)(area / items) + 1;
         if (BY < 3) BY = 3;
+        // two numbers of items that round to one length: the rows left are few
+        // or the bands many, and shorter segments gain nothing any more (bf16
+        // Box-2D3R T = 2 128 x 900000: whole columns 323 us, 15 rows 368)
         if (BY == last) break;
         last = BY;
         const double issue = Cost::issue(workgroups(BY), std::min(BY, hmax), occ, cus);
@@ -743,8 +746,12 @@ void valu2d_try(const PassArgs *ps, int n, int occ, int cus, Valu2DPick *best)
                              issue < 1.4 * 2 * points * sizeof(TS) / 1800.0;
         consider(BY, streams, std::max(issue, Cost::memory(points, BY, bx, whole_lines)));
     }
-    // fewer bands of work than one workgroup per CU: whole columns
-    if (best->cost < 0) consider(hmax, false, Cost::issue(workgroups(hmax), hmax, occ, cus));
+    // more bands than any of these numbers of items: whole columns, in each
+    // width (4 x 20000000 float32 Star-2D3R T = 4: one-column lanes 3797 us, four
+    // columns 986)
+    if (last == 0)
+        consider(hmax, false, std::max(Cost::issue(workgroups(hmax), hmax, occ, cus),
+                                       Cost::memory(points, hmax, bx, whole_lines)));
 }
 
 // Geometry of one pass for W columns per lane and segments of BY rows.

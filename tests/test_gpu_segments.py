@@ -88,3 +88,31 @@ def test_float64_lanes_within_the_registers(stl):
         p.run(x, y, 2 * T)
         ms[T] = _time(lambda: p.run(x, y, 2 * T))
     assert ms[4] <= 2.55 * ms[2], ms
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32", "f16"])
+def test_very_wide_grid(stl, dt):
+    """Rows of more bands than there are work items to deal out keep the wide
+    lanes: 12 million columns take three times as long as 4 million (one-column
+    lanes some ten times), with the oracle's values on windows."""
+    import numpy as np
+    import torch
+    import stencil_inputs as si
+    from gpu_util import U_STORE
+    from oracle import core as ocore
+    r, T, n0 = 3, 4, 5
+    w = si.normalised_weights(13, seed=7800)
+    u0, t = si.round_to(si.uniform_grid((n0, 12_000_000), seed=7810), dt)
+    ms = []
+    for n1 in (4_000_000, 12_000_000):
+        x = t[:, :n1].contiguous().cuda()
+        y = torch.empty_like(x)
+        p = stl.Plan("star", 2, r, w, (n0, n1), T=T, dtype=dt, path="valu", halo=0.25)
+        p.run(x, y, T)
+        ms.append(_time(lambda: p.run(x, y, T)))
+        for c in (0, n1 // 2, n1 - 16):
+            ref = ocore.run_window("star", 2, r, w, u0[:, :n1], T, (0, c), (n0, c + 16), "dirichlet", 0.25)
+            got = y[:, c:c + 16].to(torch.float64).cpu().numpy()
+            tol = TOL[dt] if dt in TOL else U_STORE[dt] + 2 * T * 13 * 2.0 ** -24
+            assert np.max(np.abs(got - ref)) <= tol, (n1, c)
+    assert ms[1] <= 5 * ms[0], ms
