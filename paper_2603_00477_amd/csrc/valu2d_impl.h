@@ -819,28 +819,61 @@ hipError_t launch_valu2d_batch_width(const PassArgs *ps, int n, int BY, int slot
     return hipGetLastError();
 }
 
-// Batched form: n passes (one per job) of the same variant in one launch.
+// One launch over the passes ps[0..n), or, given no staging, its pick alone.
 template <typename TS, typename TC, int SHAPE, int R, int T>
-hipError_t launch_valu2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+hipError_t valu2d_batch_list(const std::vector<PassArgs> &ps, BatchStaging *stage, hipStream_t stream, Valu2DPick *pick)
 {
-    bool any = false;
-    for (int i = 0; i < n; ++i) any = any || valu2d_points(ps[i]) > 0;
-    if (!any) return hipSuccess;
+    const int n = (int)ps.size();
     static const int occ1 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 1>);
     static const int occ2 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 2>);
     const int cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
-    Valu2DPick pick;
-    valu2d_try<TS, TC, SHAPE, R, T, 1>(ps, n, occ1, cus, &pick);
-    valu2d_try<TS, TC, SHAPE, R, T, 2>(ps, n, occ2, cus, &pick);
+    if (!stage) {
+        *pick = Valu2DPick();
+        valu2d_try<TS, TC, SHAPE, R, T, 1>(ps.data(), n, occ1, cus, pick);
+        valu2d_try<TS, TC, SHAPE, R, T, 2>(ps.data(), n, occ2, cus, pick);
+    }
     if constexpr (valu2d_widest<TC, T>() == 4) {
         static const int occ4 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 4>);
-        valu2d_try<TS, TC, SHAPE, R, T, 4>(ps, n, occ4, cus, &pick);
-        if (pick.W == 4)
-            return launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 4>(ps, n, pick.BY, occ4 * cus, stage, stream);
+        if (!stage) valu2d_try<TS, TC, SHAPE, R, T, 4>(ps.data(), n, occ4, cus, pick);
+        else if (pick->W == 4)
+            return launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 4>(ps.data(), n, pick->BY, occ4 * cus, stage, stream);
     }
-    return pick.W == 2
-               ? launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 2>(ps, n, pick.BY, occ2 * cus, stage, stream)
-               : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps, n, pick.BY, occ1 * cus, stage, stream);
+    if (!stage) return hipSuccess;
+    return pick->W == 2
+               ? launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 2>(ps.data(), n, pick->BY, occ2 * cus, stage, stream)
+               : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps.data(), n, pick->BY, occ1 * cus, stage, stream);
+}
+
+// Batched form: n passes (one per job) of the same variant in one launch, or in
+// two where grids that cannot take the widest lanes (narrow ones with rows that
+// are no whole number of vectors) would keep the others from them: when the
+// estimates of the two and 12000 cycles for a launch come to less (float32
+// Star-2D3R T = 4, 8192^2 and 64 x 71: one launch on one-column lanes 670 us a
+// pass, two launches 222).
+template <typename TS, typename TC, int SHAPE, int R, int T>
+hipError_t launch_valu2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
+{
+    constexpr int W = valu2d_widest<TC, T>();
+    std::vector<PassArgs> all, wide, other;
+    for (int i = 0; i < n; ++i) {
+        if (valu2d_points(ps[i]) <= 0) continue;
+        Valu2DJob<TC> g;
+        all.push_back(ps[i]);
+        (valu2d_bands<Valu2DCfg<TS, TC, SHAPE, R, T, W>, W>(ps[i], &g) ? wide : other).push_back(ps[i]);
+    }
+    if (all.empty()) return hipSuccess;
+    const auto list = &valu2d_batch_list<TS, TC, SHAPE, R, T>;
+    Valu2DPick one, first, second;
+    list(all, nullptr, stream, &one);
+    if (!wide.empty() && !other.empty()) {
+        list(wide, nullptr, stream, &first);
+        list(other, nullptr, stream, &second);
+        if (first.cost + second.cost + 12000.0 < one.cost) {
+            const hipError_t e = list(wide, stage, stream, &first);
+            return e == hipSuccess ? list(other, stage, stream, &second) : e;
+        }
+    }
+    return list(all, stage, stream, &one);
 }
 
 // Up to kBandBoxes boxes of one pass (the Dirichlet band of a kernel-fused

@@ -116,3 +116,27 @@ def test_very_wide_grid(stl, dt):
             tol = TOL[dt] if dt in TOL else U_STORE[dt] + 2 * T * 13 * 2.0 ** -24
             assert np.max(np.abs(got - ref)) <= tol, (n1, c)
     assert ms[1] <= 5 * ms[0], ms
+
+
+def test_narrow_grid_beside_a_wide_one(stl):
+    """A narrow grid with an odd row length, which only one-column lanes take,
+    leaves a large grid of the same batch its wide lanes (the whole batch on
+    one-column lanes takes 3.4 times as long); bits as alone."""
+    import torch
+    r, T, steps = 3, 4, 16
+    w = [1.0 / 13] * 13
+    plans, ins, outs, alone = [], [], [], []
+    for k, dims in enumerate([(8192, 8192), (64, 71), (90, 41)]):
+        plans.append(stl.Plan("star", 2, r, w, dims, T=T, dtype="f32", path="valu", boundary="periodic"))
+        g = torch.Generator(device="cuda")
+        g.manual_seed(7900 + k)
+        ins.append(torch.rand(dims, generator=g, device="cuda"))
+        outs.append(torch.empty_like(ins[-1]))
+        alone.append(torch.empty_like(ins[-1]))
+        plans[-1].run(ins[-1], alone[-1], steps)
+    stl.run_batch(plans, ins, outs, [steps] * 3)
+    one = _time(lambda: plans[0].run(ins[0], alone[0], steps))
+    all_ = _time(lambda: stl.run_batch(plans, ins, outs, [steps] * 3))
+    assert all_ <= 1.8 * one, (all_, one)
+    for a, b in zip(alone, outs):
+        assert torch.equal(a, b)
