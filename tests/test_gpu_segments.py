@@ -74,7 +74,7 @@ def test_segments_of_one_to_three_planes(stl, shape, r, T, dt):
 
 def test_float64_lanes_within_the_registers(stl):
     """Box-2D3R float64 fused four deep keeps to lanes whose accumulators leave
-    room for two waves per SIMD: a pass takes some 2.3 times one of T = 2 (2.8
+    room for two waves per SIMD: a pass takes some 2.3 times one of T = 2 (2.75
     with four columns per lane and one wave)."""
     import torch
     dims = (8192, 8192)
@@ -85,9 +85,9 @@ def test_float64_lanes_within_the_registers(stl):
     ms = {}
     for T in (2, 4):
         p = stl.Plan("box", 2, 3, w, dims, T=T, dtype="f64", path="valu")
-        p.run(x, y, 2 * T)
-        ms[T] = _time(lambda: p.run(x, y, 2 * T))
-    assert ms[4] <= 2.55 * ms[2], ms
+        p.run(x, y, 8 * T)
+        ms[T] = _time(lambda: p.run(x, y, 8 * T))
+    assert ms[4] <= 2.5 * ms[2], ms
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32", "f16"])
