@@ -215,7 +215,7 @@ struct BandCols {
 // 2:4 structured-sparse instructions, one per pair of kernel columns (16-bit
 // operands, composite radius <= 7; layout in mfma_layout.h).
 template <int DT, int SHAPE, int r, int T, int V, int NW, bool SP = false>
-__device__ __forceinline__ void mfma2d_tile(const Mfma2DArgs &a, const int tile)
+__device__ __forceinline__ void mfma2d_tile(const Mfma2DArgs &a, const int tile, const int tid)
 {
     using Cfg = Mfma2DCfg<DT, SHAPE, r, T, V, NW, SP>;
     using MT = typename Cfg::MT;
@@ -240,7 +240,6 @@ __device__ __forceinline__ void mfma2d_tile(const Mfma2DArgs &a, const int tile)
     using FRS = typename MT::FR;
     __shared__ __attribute__((aligned(16))) FRS lA[ALDS ? NAF * 64 : 1];
 
-    const int tid = threadIdx.x;
     const int tr = tile / a.ntc, tcn = tile - tr * a.ntc;
     const int r0 = tr * Cfg::TR, c0 = tcn * Cfg::TCOL;
     const int n0 = a.n0, n1 = a.n1;
@@ -821,7 +820,7 @@ struct RowsCfg {
 // prefetching its next tile's frame under the current tile's MFMAs, measured
 // 2x slower on 16384^2: the dispatcher balances tiles over CUs better).
 template <int DT, int SHAPE, int r, int T, int V, int NW>
-__device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int tile)
+__device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int tile, const int tid)
 {
     using C = RowsCfg<DT, SHAPE, r, T, V, NW>;
     using FR = typename C::FR;
@@ -830,7 +829,6 @@ __device__ __forceinline__ void mfma2d_rows_tile(const Mfma2DArgs &a, const int 
     constexpr int NTAB = NFRAG * 64 * (C::X3 ? 2 : 1);  // hi table, then lo table
     __shared__ __attribute__((aligned(16))) OP lb[C::FRAME * (C::X3 ? 2 : 1)];
     __shared__ __attribute__((aligned(16))) FR lA[C::ALDS ? NTAB : 1];
-    const int tid = threadIdx.x;
     const FR *afr = static_cast<const FR *>(a.afrag);
 
     // A table: loads in flight during the staging
@@ -880,9 +878,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW >= 1
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     if (tile >= a.ntiles) return;
     if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-        mfma2d_rows_tile<DT, SHAPE, r, T, V, NW>(a, tile);
+        mfma2d_rows_tile<DT, SHAPE, r, T, V, NW>(a, tile, threadIdx.x);
     else
-        mfma2d_tile<DT, SHAPE, r, T, V, NW, SP>(a, tile);
+        mfma2d_tile<DT, SHAPE, r, T, V, NW, SP>(a, tile, threadIdx.x);
 }
 
 // Persistent batched launch over the tiles of several jobs: workgroup b takes
@@ -897,11 +895,35 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW >= 1
     int j = 0;
     for (int item = xcd_remap(blockIdx.x, gridDim.x); item < total; item += gridDim.x) {
         while (j + 1 < njobs && tile_start[j + 1] <= item) ++j;
-        const Mfma2DArgs a = jobs[j];
+        // The sixteen-wave tiles have 64 registers: the job comes by scalar loads,
+        // and the thread id is opaque, so that what depends on it alone (each
+        // chunk's row and column) is worked out again for every item.  Kept in
+        // registers across the loop these took 12-96 bytes of scratch (two 8192^2
+        // grids, bf16 Box-2D2R: T = 2 212 us a pass, 153 so; T = 4 233 and 180),
+        // and up to 144 in the compensated column layout (Box-2D3R T = 4 1695 and
+        // 989 us).  The smaller row tiles have the room (2048^2 bf16 Box-2D2R
+        // T = 4 23.1 us, 27.2 so).
+        int tid = threadIdx.x;
+        Mfma2DArgs a;
+        if constexpr (NW >= 16 || (MfmaTypes<DT>::X3 && !use_rows<DT, SHAPE, r, T, SP>())) {
+            asm volatile("" : "+v"(tid));
+            const JobPtr<Mfma2DArgs> job = job_entry(jobs, j);
+            a.src = job->src;
+            a.dst = job->dst;
+            a.afrag = job->afrag;
+            a.afrag_lo = job->afrag_lo;
+            a.n0 = job->n0;
+            a.n1 = job->n1;
+            a.ntc = job->ntc;
+            a.periodic = job->periodic;
+            a.h = job->h;
+        } else {
+            a = jobs[j];
+        }
         if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-            mfma2d_rows_tile<DT, SHAPE, r, T, V, NW>(a, item - tile_start[j]);
+            mfma2d_rows_tile<DT, SHAPE, r, T, V, NW>(a, item - tile_start[j], tid);
         else
-            mfma2d_tile<DT, SHAPE, r, T, V, NW, SP>(a, item - tile_start[j]);
+            mfma2d_tile<DT, SHAPE, r, T, V, NW, SP>(a, item - tile_start[j], tid);
         __syncthreads();
     }
 }

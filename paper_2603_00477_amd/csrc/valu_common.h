@@ -23,6 +23,17 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb)
     return (bid % kNumXcd) * per + bid / kNumXcd;
 }
 
+// Entry j (the same for the whole wave) of a batched launch's job table, which
+// the kernel only reads: through the constant address space its fields come by
+// scalar loads.  Copied through a generic pointer they take vector registers.
+template <typename Job>
+using JobPtr = const __attribute__((address_space(4))) Job *;
+template <typename Job>
+__device__ __forceinline__ JobPtr<Job> job_entry(const Job *jobs, int j)
+{
+    return (JobPtr<Job>)(jobs + __builtin_amdgcn_readfirstlane(j));
+}
+
 __device__ __forceinline__ int wrap(int i, int n)
 {
     int m = i % n;
