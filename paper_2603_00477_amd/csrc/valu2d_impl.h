@@ -114,6 +114,12 @@ struct Valu2DCfg {
     // with more registers from it and are 5-15 % slower at 512^2; Box-2D3R
     // T = 4, which spans both register files, 8 % at 8192^2.
     static constexpr bool FIRST_FROM_ZERO = sizeof(TC) == 8 && W == 4 && !(WCOL && T * Q > 24);
+    // Batched kernels whose accumulators take 64 registers and more read their
+    // job by scalar loads; copied through vector registers it cost them a wave
+    // per SIMD (two 8192^2 grids, float64 Star-2D2R T = 4: 272 registers and 810 us
+    // a pass, 249 and 534; Star-2D3R T = 3 782 and 521).  Lighter ones lose 7 % to
+    // the waves they gain (float64 Star-2D1R T = 2 471 us, 505 so).
+    static constexpr bool SCALAR_JOB = T * Q * W * (int)sizeof(TC) / 4 >= 64;
 };
 
 // Weights in constant memory (scalar loads).
@@ -476,8 +482,8 @@ __device__ __forceinline__ void valu2d_tile(const Valu2DJob<TC> &a,
 // compiler spills them to vector lanes and pays a readlane per use.
 // The float64 Star-2D7R set (29 weights) stays in scalar registers: pinned in
 // vector registers beside its 15 accumulator rows per stage it needs all 256.
-template <typename TC, int K, bool SCALAR64 = false, typename SrcT>
-__device__ __forceinline__ void load_weights(TC (&wk)[K], const SrcT *w)
+template <typename TC, int K, bool SCALAR64 = false, typename Src>
+__device__ __forceinline__ void load_weights(TC (&wk)[K], Src w)
 {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -525,6 +531,33 @@ struct Valu2DBatchJob {
     TC w[K];
 };
 
+// Geometry of a batched job, by scalar loads or copied through vector registers.
+template <typename TC, bool SCALAR, typename Job>
+__device__ __forceinline__ Valu2DJob<TC> valu2d_job(const Job *entry, JobPtr<Job> job)
+{
+    Valu2DJob<TC> g;
+    if constexpr (SCALAR) {
+        g.src = job->g.src;
+        g.dst = job->g.dst;
+        g.n0 = job->g.n0;
+        g.n1 = job->g.n1;
+        g.oy0 = job->g.oy0;
+        g.oy1 = job->g.oy1;
+        g.ox0 = job->g.ox0;
+        g.ox1 = job->g.ox1;
+        g.BX = job->g.BX;
+        g.BY = job->g.BY;
+        g.nbands = job->g.nbands;
+        g.nsegs = job->g.nsegs;
+        g.anchor = job->g.anchor;
+        g.periodic = job->g.periodic;
+        g.h = job->g.h;
+    } else {
+        g = entry->g;
+    }
+    return g;
+}
+
 // Persistent batched launch: the workgroups walk one list of (job, band
 // group x segment) items spanning every job of the batch (jobs of uneven
 // sizes); workgroup b takes items b + i*gridDim.  tile_start[j] is the first
@@ -540,17 +573,19 @@ __global__ __launch_bounds__(64 * kValu2DWaves) void valu2d_batch_kernel(
     int j = 0;
     for (int item = xcd_remap(blockIdx.x, gridDim.x); item < total; item += gridDim.x) {
         while (j + 1 < njobs && tile_start[j + 1] <= item) ++j;
-        const Valu2DJob<TC> g = jobs[j].g;
+        const auto job = job_entry(jobs, j);
+        const Valu2DJob<TC> g = valu2d_job<TC, Cfg::SCALAR_JOB>(jobs + j, job);
         const int local = valu2d_item(item - tile_start[j]);
         if (local >= g.nbands * g.nsegs) continue;
         const int seg = local / g.nbands, band = local - seg * g.nbands;
         TC wk[Cfg::WPTR ? 1 : Cfg::K];
         ConstPtr<TC> wp = nullptr;
         if constexpr (Cfg::WPTR) {
-            wp = (ConstPtr<TC>)(jobs[j].w);  // the job table is read-only in the kernel
+            wp = &job->w[0];
             wk[0] = TC(0);
         } else {
-            load_weights<TC, Cfg::K, SHAPE == STENCIL_STAR && R == 7>(wk, jobs[j].w);
+            if constexpr (Cfg::SCALAR_JOB) load_weights<TC, Cfg::K, SHAPE == STENCIL_STAR && R == 7>(wk, &job->w[0]);
+            else load_weights<TC, Cfg::K, SHAPE == STENCIL_STAR && R == 7>(wk, jobs[j].w);
         }
         valu2d_tile<TS, TC, SHAPE, R, T, W>(g, wk, wp, band, seg, lane);
     }
@@ -819,29 +854,48 @@ hipError_t launch_valu2d_batch_width(const PassArgs *ps, int n, int BY, int slot
     return hipGetLastError();
 }
 
-// One launch over the passes ps[0..n), or, given no staging, its pick alone.
+// Resident workgroups per CU of the batched kernels of 1, 2 and 4 columns.
 template <typename TS, typename TC, int SHAPE, int R, int T>
-hipError_t valu2d_batch_list(const std::vector<PassArgs> &ps, BatchStaging *stage, hipStream_t stream, Valu2DPick *pick)
+const int *valu2d_batch_occ()
 {
-    const int n = (int)ps.size();
-    static const int occ1 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 1>);
-    static const int occ2 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 2>);
-    const int cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
-    if (!stage) {
-        *pick = Valu2DPick();
-        valu2d_try<TS, TC, SHAPE, R, T, 1>(ps.data(), n, occ1, cus, pick);
-        valu2d_try<TS, TC, SHAPE, R, T, 2>(ps.data(), n, occ2, cus, pick);
-    }
-    if constexpr (valu2d_widest<TC, T>() == 4) {
-        static const int occ4 = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 4>);
-        if (!stage) valu2d_try<TS, TC, SHAPE, R, T, 4>(ps.data(), n, occ4, cus, pick);
-        else if (pick->W == 4)
-            return launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 4>(ps.data(), n, pick->BY, occ4 * cus, stage, stream);
-    }
-    if (!stage) return hipSuccess;
-    return pick->W == 2
-               ? launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 2>(ps.data(), n, pick->BY, occ2 * cus, stage, stream)
-               : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps.data(), n, pick->BY, occ1 * cus, stage, stream);
+    static const struct Occ {
+        int v[3] = {valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 1>),
+                    valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 2>), 1};
+        Occ()
+        {
+            if constexpr (valu2d_widest<TC, T>() == 4)
+                v[2] = valu2d_occupancy(valu2d_batch_kernel<TS, TC, SHAPE, R, T, 4>);
+        }
+    } occ;
+    return occ.v;
+}
+
+// Width and segments of one batched launch over the passes `ps`.
+template <typename TS, typename TC, int SHAPE, int R, int T>
+Valu2DPick valu2d_batch_pick(const std::vector<PassArgs> &ps)
+{
+    const int *occ = valu2d_batch_occ<TS, TC, SHAPE, R, T>();
+    const int n = (int)ps.size(), cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
+    Valu2DPick pick;
+    valu2d_try<TS, TC, SHAPE, R, T, 1>(ps.data(), n, occ[0], cus, &pick);
+    valu2d_try<TS, TC, SHAPE, R, T, 2>(ps.data(), n, occ[1], cus, &pick);
+    if constexpr (valu2d_widest<TC, T>() == 4)
+        valu2d_try<TS, TC, SHAPE, R, T, 4>(ps.data(), n, occ[2], cus, &pick);
+    return pick;
+}
+
+template <typename TS, typename TC, int SHAPE, int R, int T>
+hipError_t valu2d_batch_go(const std::vector<PassArgs> &ps, const Valu2DPick &pick, BatchStaging *stage,
+                           hipStream_t stream)
+{
+    const int *occ = valu2d_batch_occ<TS, TC, SHAPE, R, T>();
+    const int n = (int)ps.size(), cus = ps[0].num_cu > 0 ? ps[0].num_cu : 256;
+    if constexpr (valu2d_widest<TC, T>() == 4)
+        if (pick.W == 4)
+            return launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 4>(ps.data(), n, pick.BY, occ[2] * cus, stage, stream);
+    return pick.W == 2
+               ? launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 2>(ps.data(), n, pick.BY, occ[1] * cus, stage, stream)
+               : launch_valu2d_batch_width<TS, TC, SHAPE, R, T, 1>(ps.data(), n, pick.BY, occ[0] * cus, stage, stream);
 }
 
 // Batched form: n passes (one per job) of the same variant in one launch, or in
@@ -862,18 +916,17 @@ hipError_t launch_valu2d_batch(const PassArgs *ps, int n, BatchStaging *stage, h
         (valu2d_bands<Valu2DCfg<TS, TC, SHAPE, R, T, W>, W>(ps[i], &g) ? wide : other).push_back(ps[i]);
     }
     if (all.empty()) return hipSuccess;
-    const auto list = &valu2d_batch_list<TS, TC, SHAPE, R, T>;
-    Valu2DPick one, first, second;
-    list(all, nullptr, stream, &one);
+    const auto pick = &valu2d_batch_pick<TS, TC, SHAPE, R, T>;
+    const auto go = &valu2d_batch_go<TS, TC, SHAPE, R, T>;
+    const Valu2DPick one = pick(all);
     if (!wide.empty() && !other.empty()) {
-        list(wide, nullptr, stream, &first);
-        list(other, nullptr, stream, &second);
+        const Valu2DPick first = pick(wide), second = pick(other);
         if (first.cost + second.cost + 12000.0 < one.cost) {
-            const hipError_t e = list(wide, stage, stream, &first);
-            return e == hipSuccess ? list(other, stage, stream, &second) : e;
+            const hipError_t e = go(wide, first, stage, stream);
+            return e == hipSuccess ? go(other, second, stage, stream) : e;
         }
     }
-    return list(all, stage, stream, &one);
+    return go(all, one, stage, stream);
 }
 
 // Up to kBandBoxes boxes of one pass (the Dirichlet band of a kernel-fused
