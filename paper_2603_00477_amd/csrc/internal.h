@@ -47,7 +47,6 @@ struct PassArgs {
     const void *afrag_lo;    // compensated mode: lo parts
     int R;                   // MFMA composite radius (r * steps)
     int num_cu;
-    int slots_per_cu;        // resident workgroups per CU of the launched kernel (0 = unknown)
 };
 
 // Device copies of small host tables (job lists of batched launches).  put()
@@ -96,6 +95,7 @@ struct KernelEntry {
     int d;
     int r;       // -1 = any
     int t;       // steps per pass, -1 = any
+    // one pass; null where the variant only redoes bands (launch_boxes)
     hipError_t (*launch)(const PassArgs &, hipStream_t);
     // n passes of this variant (different grids) in one persistent launch; may be null
     hipError_t (*launch_batch)(const PassArgs *, int, BatchStaging *, hipStream_t) = nullptr;

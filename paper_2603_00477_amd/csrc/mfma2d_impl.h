@@ -950,10 +950,9 @@ struct RowsSmall {
 struct RowsLarge {
     static constexpr int V = 5, NW = 16;
 };
-template <int DT>
-bool rows_large(const PassArgs *ps, int n)
+// (the compensated mode keeps the small tiles)
+inline bool rows_large(const PassArgs *ps, int n)
 {
-    if (MfmaTypes<DT>::X3) return false;
     double bytes = 0;
     for (int i = 0; i < n; ++i) bytes += 4.0 * ps[i].dims[0] * ps[i].dims[1];  // 2 bytes in, 2 out
     return bytes > 256e6;
@@ -993,10 +992,11 @@ hipError_t launch_mfma2d_shape(const PassArgs &p, hipStream_t stream)
 template <int DT, int SHAPE, int r, int T, bool SP = false>
 hipError_t launch_mfma2d(const PassArgs &p, hipStream_t stream)
 {
-    if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-        return rows_large<DT>(&p, 1) ? launch_mfma2d_shape<DT, SHAPE, r, T, RowsLarge, SP>(p, stream)
-                                 : launch_mfma2d_shape<DT, SHAPE, r, T, RowsSmall, SP>(p, stream);
-    else
+    if constexpr (use_rows<DT, SHAPE, r, T, SP>()) {
+        if constexpr (!MfmaTypes<DT>::X3)
+            if (rows_large(&p, 1)) return launch_mfma2d_shape<DT, SHAPE, r, T, RowsLarge, SP>(p, stream);
+        return launch_mfma2d_shape<DT, SHAPE, r, T, RowsSmall, SP>(p, stream);
+    } else
         return launch_mfma2d_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(p, stream);
 }
 
@@ -1034,10 +1034,12 @@ hipError_t launch_mfma2d_batch_shape(const PassArgs *ps, int n, BatchStaging *st
 template <int DT, int SHAPE, int r, int T, bool SP = false>
 hipError_t launch_mfma2d_batch(const PassArgs *ps, int n, BatchStaging *stage, hipStream_t stream)
 {
-    if constexpr (use_rows<DT, SHAPE, r, T, SP>())
-        return rows_large<DT>(ps, n) ? launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsLarge, SP>(ps, n, stage, stream)
-                                 : launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsSmall, SP>(ps, n, stage, stream);
-    else
+    if constexpr (use_rows<DT, SHAPE, r, T, SP>()) {
+        if constexpr (!MfmaTypes<DT>::X3)
+            if (rows_large(ps, n))
+                return launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsLarge, SP>(ps, n, stage, stream);
+        return launch_mfma2d_batch_shape<DT, SHAPE, r, T, RowsSmall, SP>(ps, n, stage, stream);
+    } else
         return launch_mfma2d_batch_shape<DT, SHAPE, r, T, Mfma2DShape<DT>, SP>(ps, n, stage, stream);
 }
 

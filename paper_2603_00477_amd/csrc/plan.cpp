@@ -387,7 +387,7 @@ hipError_t launch_fixup(const stencil_plan_s *p, int t, const void *src, void *d
 {
     // for bf16x3 this finds the float-storage, FP64-arithmetic VALU variant
     const KernelEntry *k = find_kernel(STENCIL_PATH_VALU, p->dtype, p->shape, p->d, p->r, t);
-    if (!k) return hipErrorNotSupported;
+    if (!k || (!k->launch && !k->launch_boxes)) return hipErrorNotSupported;
     const int band = p->r * (t - 1);
     PassArgs boxes[2 * kMaxD];
     int nboxes = 0;
@@ -444,7 +444,7 @@ int run_one(stencil_plan_s *p, const void *in, void *out, int64_t steps, hipStre
     for (int i = 0; i < P; ++i) {
         void *dst = ((P - 1 - i) % 2 == 0) ? out : scratch;
         const PassDesc &pd = passes[i];
-        if (!pd.k) return fail(STENCIL_ERR_UNSUPPORTED, "no kernel for a pass");
+        if (!pd.k || !pd.k->launch) return fail(STENCIL_ERR_UNSUPPORTED, "no kernel for a pass");
         PassArgs a = base_args(p, pd.t);
         a.src = src;
         a.dst = dst;
@@ -515,7 +515,7 @@ int run_batch(int n, const stencil_plan_t *plans, const void *const *ins, void *
             const int P = (int)ps.size();
             void *dst = ((P - 1 - (int)j) % 2 == 0) ? outs[i] : p->scratch;
             const PassDesc &pd = ps[j];
-            if (!pd.k) return fail(STENCIL_ERR_UNSUPPORTED, "no kernel for a pass");
+            if (!pd.k || !pd.k->launch) return fail(STENCIL_ERR_UNSUPPORTED, "no kernel for a pass");
             PassArgs a = base_args(p, pd.t);
             a.src = src[i];
             a.dst = dst;

@@ -992,6 +992,14 @@ constexpr hipError_t (*valu2d_band_launcher())(const PassArgs *, int, hipStream_
 #define V2(TS, TC, DT, SH, R, T) \
     {STENCIL_PATH_VALU, DT, SH, 2, R, T, &launch_valu2d<TS, TC, SH, R, T>, \
      &launch_valu2d_batch<TS, TC, SH, R, T>, valu2d_band_launcher<TS, TC, SH, R, T>()}
+// Variants that only redo the Dirichlet band of a matrix pass.
+#define V2_BAND(TS, TC, DT, SH, R, T) \
+    {STENCIL_PATH_VALU, DT, SH, 2, R, T, nullptr, nullptr, valu2d_band_launcher<TS, TC, SH, R, T>()}
+#define V2_BAND_T(TS, TC, DT, SH, R) \
+    V2_BAND(TS, TC, DT, SH, R, 1), V2_BAND(TS, TC, DT, SH, R, 2), V2_BAND(TS, TC, DT, SH, R, 3), V2_BAND(TS, TC, DT, SH, R, 4)
+#define V2_BAND_R(TS, TC, DT, SH) \
+    V2_BAND_T(TS, TC, DT, SH, 1), V2_BAND_T(TS, TC, DT, SH, 2), V2_BAND_T(TS, TC, DT, SH, 3)
+#define V2_BAND_S(TS, TC, DT) V2_BAND_R(TS, TC, DT, STENCIL_STAR), V2_BAND_R(TS, TC, DT, STENCIL_BOX)
 #define V2_T(TS, TC, DT, SH, R) \
     V2(TS, TC, DT, SH, R, 1), V2(TS, TC, DT, SH, R, 2), V2(TS, TC, DT, SH, R, 3), V2(TS, TC, DT, SH, R, 4)
 #define V2_R(TS, TC, DT, SH) V2_T(TS, TC, DT, SH, 1), V2_T(TS, TC, DT, SH, 2), V2_T(TS, TC, DT, SH, 3)

@@ -65,3 +65,25 @@ def test_no_kernel_spills_to_scratch():
                 bad.append((k[".name"], k[".private_segment_fixed_size"]))
     assert total > 500
     assert not bad, bad[:5]
+
+
+def test_compensated_passes_have_matrix_kernels():
+    """The vector kernels of the compensated mode only redo bands: every plan of
+    it that can be made has a matrix kernel at each depth its runs may use, and
+    no three-dimensional plan of it exists."""
+    import paper_2603_00477_amd as stl
+    made = 0
+    for shape in ("star", "box"):
+        for d in (2, 3):
+            for r in (1, 2, 3, 4, 7):
+                K = (2 * r + 1) ** d if shape == "box" else 2 * d * r + 1
+                for T in range(1, 9):
+                    try:
+                        stl.Plan(shape, d, r, [1.0 / K] * K, (64,) * d, T=T, dtype="bf16x3")
+                    except stl.StencilError:
+                        continue
+                    made += 1
+                    assert d == 2
+                    for t in range(1, T + 1):
+                        assert stl.kernel_available("mfma", "bf16x3", shape, d, r, t), (shape, r, T, t)
+    assert made >= 24
