@@ -570,6 +570,15 @@ hipError_t launch_fused3d(const PassArgs &p, hipStream_t stream)
     Rows3DArgs<TC, Cfg::K> a;
     hipError_t err;
     if (!rows3d_args<Cfg, TC, S::WY>(p, pick, &a, &err)) return err;
+    if ((int64_t)a.ntiles * 64 * pick.nw > UINT32_MAX) {
+        // a launch takes less than 2^32 threads (one column a lane: some 1.5e10
+        // points in a plane or two): the halves of the box after each other
+        const int ax = b.d1 >= b.d2 ? 1 : 2, mid = p.region_lo[ax] + (ax == 1 ? b.d1 : b.d2) / 2;
+        PassArgs lower = p, upper = p;
+        lower.region_hi[ax] = upper.region_lo[ax] = mid;
+        err = launch_fused3d<TC, SHAPE, R, T>(lower, stream);
+        return err == hipSuccess ? launch_fused3d<TC, SHAPE, R, T>(upper, stream) : err;
+    }
     err = rows3d_allow_lds<Cfg>(kernel, pick.nw);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kernel, dim3(a.ntiles), dim3(64 * pick.nw), Cfg::lds_bytes(pick.nw), stream, a);

@@ -140,3 +140,38 @@ def test_narrow_grid_beside_a_wide_one(stl):
     assert all_ <= 1.8 * one, (all_, one)
     for a, b in zip(alone, outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("shape,r,T,dims", [("star", 1, 2, (1, 131072, 131072)), ("star", 1, 1, (1, 131072, 131071))])
+def test_planes_of_more_threads_than_a_launch_takes(stl, shape, r, T, dims):
+    """A plane of 1.7e10 points (one column a lane makes 4.4e9 to 4.9e9 threads):
+    windows at the corners and around the middle row and column against the
+    oracle on blocks that hold what they depend on."""
+    import torch
+    import stencil_inputs as si
+    if torch.cuda.mem_get_info()[0] < 180 << 30:
+        pytest.skip("needs 140 GB of free device memory")
+    w = si.normalised_weights(7, seed=8000)
+    n0, n1, n2 = dims
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8010)
+    x = torch.rand(dims, generator=g, device="cuda", dtype=torch.float32)
+    y = torch.full(dims, float("nan"), device="cuda", dtype=torch.float32)
+    p = stl.Plan(shape, 3, r, w, dims, T=T, dtype="f32", path="valu", halo=0.25)
+    p.run(x, y, T)
+    torch.cuda.synchronize()
+    m = r * T
+    for cy in (0, n1 // 4, n1 // 2, n1):
+        for cx in (0, n2 // 2, n2):
+            lo = [max(cy - 20, 0), max(cx - 20, 0)]
+            hi = [min(cy + 20, n1), min(cx + 20, n2)]
+            a = [max(v - m, 0) for v in lo]
+            e = [min(hi[0] + m, n1), min(hi[1] + m, n2)]
+            block = x[:, a[0]:e[0], a[1]:e[1]].to(torch.float64).cpu().numpy()
+            ref = oracle(shape, 3, r, w, block, T, "dirichlet", 0.25)
+            ref = ref[:, lo[0] - a[0]:hi[0] - a[0], lo[1] - a[1]:hi[1] - a[1]]
+            got = y[:, lo[0]:hi[0], lo[1]:hi[1]].to(torch.float64).cpu().numpy()
+            assert rel_inf(got, ref) <= TOL["f32"], (cy, cx)
+    assert not torch.isnan(y[0, ::4096, ::511]).any()
+    del x, y
+    torch.cuda.empty_cache()
