@@ -3,6 +3,10 @@
 // "Tensor Core Implementation with Kernel Fusion": executed work (alpha/S)
 // t C, memory traffic unchanged).
 //
+// Two layouts: the column layout described here (float64, float32, the 2:4
+// sparse instructions, 16-bit composites with a large operand table) and the
+// row layout of RowsCfg below (the other 16-bit and compensated passes).
+//
 // Workgroup: NW waves side by side; wave w owns V stacked 16 x 16 output
 // tiles (16V rows x 16 columns).  The input block the workgroup needs
 // ((16V + 2R) x (16 NW + 2R) points, halo included, boundary rule applied) is
@@ -587,10 +591,15 @@ __device__ __forceinline__ void mfma2d_tile(const Mfma2DArgs &a, const int tile,
 // tiles interleave their rows (tile v holds rows V ln + v), so that one
 // operand-B read serves up to V of them.
 //
-// What bounds it: HBM latency, then the matrix units (bf16 Box-2D2R 16384^2:
-// T = 1 / 2 / 4 253 / 271 / 290 us a pass of 1.07 GB, 4.2 TB/s at T = 1; 17
-// MFMAs per 16 x 16 tile take about 126 us at T = 4).  Before the interleaved
-// rows and sixteen-wave tiles: 271 / 305 / 365 us.
+// What bounds it: no single unit.  bf16 Box-2D2R 16384^2, T = 1 / 2 / 4: 253 /
+// 271 / 290 us a pass of 1.07 GB.  Counters there: matrix units busy 14 / 23 /
+// 45 % (17 MFMAs per 16 x 16 tile take about 126 us at T = 4), LDS 11 / 15 /
+// 24 % without bank conflicts, HBM at 3.8-4.2 of the 4.9 TB/s of a copy; the
+// six waves a SIMD wait 41-50 % of their cycles, LDS a twentieth of that, the
+// rest between the phases of a tile (loads to the staging store, its barriers,
+// the stores).  The compensated mode: T = 1-2 at the copy rate (4.7-5.0 TB/s),
+// T = 4 62 % matrix busy.  Before the interleaved rows and sixteen-wave tiles
+// bf16 took 271 / 305 / 365 us.
 template <int DT, int SHAPE, int r, int T, int V, int NW>
 struct RowsCfg {
     using MT = MfmaTypes<DT>;
@@ -691,10 +700,9 @@ struct RowsCfg {
             if (e < LRD * NCH) put_chunk(v[i], lb, row * PIT + 8 * ch);
         }
     }
-    // edge tiles: a chunk inside
-    // the grid (after the periodic wrap of its first column) is one load at
-    // element alignment, one outside a Dirichlet grid is h, and only a chunk
-    // that straddles an edge goes element by element.  All chunks load
+    // edge tiles: a chunk inside the grid (after the periodic wrap of its first
+    // column) is one load at element alignment, one outside a Dirichlet grid is
+    // h, and only a chunk that straddles an edge goes element by element.  All chunks load
     // unconditionally (a valid dummy where they must not), so the loads stay in
     // flight together.  Columns past the data (read only against zero
     // weights) get zeros.

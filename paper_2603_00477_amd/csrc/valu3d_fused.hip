@@ -27,15 +27,19 @@
 // What bounds it: vector issue.  Keeping a wave's own rows in registers leaves
 // 2R row reads and at most WY row writes of LDS per plane and stage, where
 // reading the whole (WY+2R) x (W+2R) window from LDS had made LDS the limit.
-// 512^3 periodic, GStencil/s, window-from-LDS kernel -> this one:
-//   float32  Star-3D1R T2 833 -> 938     float64  Star-3D2R T2 432 -> 535
-//            Star-3D2R T2 846 -> 866              Star-3D2R T3 461 -> 545
-//            Star-3D2R T3 956 -> 1131             Star-3D3R T2 323 -> 390
-//            Star-3D3R T2 553 -> 761              Box-3D1R  T2 406 -> 516
-//            Box-3D1R  T2 651 -> 828              Box-3D1R  T3 416 -> 568
-//            Box-3D1R  T3 726 -> 848
-// and 97^3 float32 Star-3D1R T2 150 -> 9 us a pass: small grids need narrow
-// tiles and short segments to reach every CU (see rows3d_pick).
+// 512^3 Dirichlet, us a pass, window-from-LDS kernel -> this one:
+//   float32  Star-3D1R T2 299 -> 283     float64  Star-3D2R T2 607 -> 531
+//            Star-3D2R T2 329 -> 321              Star-3D2R T3 863 -> 756
+//            Star-3D2R T3 433 -> 398              Star-3D3R T2 833 -> 751
+//            Star-3D3R T2 492 -> 417              Box-3D1R  T2 673 -> 587
+//            Box-3D1R  T2 429 -> 355              Box-3D1R  T3 1009 -> 812
+//            Box-3D1R  T3 570 -> 513
+// and 97^3 float32 Star-3D1R T2 149 -> 7.8 us a pass: small grids need narrow
+// tiles and short segments to reach every CU (see rows3d_pick).  Counters at
+// 512^3 periodic: float32 and the float64 boxes issue vector instructions in
+// 66-101 % of the cycles; the float64 Star-3D2R passes in 46-59 %, since their
+// rows leave registers for 1.8 waves a SIMD.  LDS is busy in 4-46 %, without
+// bank conflicts.
 
 #include <hip/hip_runtime.h>
 
@@ -634,7 +638,7 @@ hipError_t launch_fused3d_batch(const PassArgs *ps, int n, BatchStaging *stage, 
 // cache (256 MB) holds much of a pass, and for other row lengths the narrow
 // tiles above win (256^3 float32 Star-3D1R 33 vs 27 us, 333^3 120 vs 72, 97^3
 // 40 vs 7.5).  Float64 Star-3D3R is bound by its arithmetic and wins at every
-// size (512^3 533 vs 462 us).
+// size (512^3 524 vs 517 us, 97^3 48 vs 12.7).
 template <typename TC, int R>
 bool one_step_streams(const PassArgs &p)
 {
