@@ -268,8 +268,8 @@ typedef struct {
     int scenario;        /* 1 MB->MB, 2 MB->CB, 3 CB->MB, 4 CB->CB            */
     int sweet_spot;      /* alpha*gamma < S PP_mfma / PP_valu                 */
     int winner;          /* -1 VALU, 0 tie (ratio in [0.87, 1.15]), +1 MFMA    */
-    /* Halo terms of this library's tilings (the paper's model omits halos and
-     * attributes measured excess work to their recomputation):              */
+    /* Halo terms, of one fixed reference tiling per case (the paper's model
+     * omits halos and attributes measured excess work to recomputing them): */
     double halo_valu;    /* executed / useful VALU FMAs in the tile plane: the
                             ring each fused tile recomputes (r*T points per
                             side in 2D; r*(T-1) in 3D, whose input halo is

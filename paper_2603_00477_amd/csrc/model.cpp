@@ -90,15 +90,15 @@ MfmaLayout mfma_layout(int shape, int d, int r, int steps, int dtype)
 // Skirt recomputation of the VALU path's fused tiles: executed / useful FMAs,
 // for one reference layout per case.  The launchers pick lane widths and tiles
 // per grid; the model keeps these fixed values (they are part of its output),
-// which depend on the problem alone.  2D: a wave's band of 64 W columns (W = 16-byte vector) keeps
-// 64 W - 2 E outputs, E = r T rounded up to W.  3D: an in-plane tile of
-// (TY WY) x (TX W) points keeps (TY WY - 2 EY) x (TX W - 2 EX), EY = r T for
-// fused passes (one-step passes stage their halo: no skirt).
+// which depend on the problem alone.  2D: a band of 64 W columns (W = 16-byte
+// vector) keeps 64 W - 2 E outputs, E = r T rounded up to W.  3D: an in-plane
+// tile of L1 x M1 points less its margins for fused passes; one-step passes
+// stage their halo and recompute nothing.
 static double valu_halo_factor(int shape, int d, int r, int T, int dtype)
 {
     const int D = dtype_bytes(dtype);
     const int W16 = 16 / D > 8 ? 8 : 16 / D;
-    // columns per lane of the 2D kernel: one 16-byte vector, two for float64
+    // columns per lane of the reference band: one 16-byte vector, two for float64
     // at T = 2 and for float64 r = 7 at T = 1
     const int W = (d == 2 && D == 8 && (T == 2 || (T == 1 && r >= 7))) ? 2 * W16 : W16;
     if (d == 2) {
@@ -106,10 +106,9 @@ static double valu_halo_factor(int shape, int d, int r, int T, int dtype)
         return (64.0 * W) / (64.0 * W - 2.0 * E);
     }
     if (T == 1) return 1.0;
-    // fused 3D passes: every step computes the L1 x M1 layout (2 rows x W
-    // columns per thread; stars 16 x 32 threads, boxes 32 rows x 64 columns);
-    // the input halo is staged, so the output tile is the layout less
-    // r (T - 1) per side, the left margin rounded up to a whole vector
+    // fused 3D passes: every step computes the reference tile of L1 x M1 points
+    // (stars 64 x 16 W, boxes 32 x 64) with its input halo staged, so the output
+    // tile is r (T - 1) less per side, the left margin rounded up to a vector
     const int L1 = 2 * (shape == STENCIL_STAR ? 32 : 16), M1 = shape == STENCIL_STAR ? 16 * W : 64;
     const int SK = r * (T - 1), SKL = (SK + W - 1) / W * W;
     const int BY = L1 - 2 * SK, BX = (M1 - SKL - SK) / W * W;
